@@ -27,6 +27,10 @@ constexpr int kWalkTable = 8 * kWalkThreads;     // block-local leaf table: at m
 constexpr int kLeafThreads = 256;
 constexpr int kLeafBatch = 8;                // loads in flight per thread in the leaf kernel
 constexpr int kLeafLdsPairs = kLeafBatch * kLeafThreads;  // pairs a leaf holds in LDS at once
+// Binned frames: bucketed (then binned) pairs per work item of a large leaf.
+// Whole bins are dealt, so an item may hold up to a bin more; a quarter of LDS
+// is left for that.
+constexpr int kRangePairs = kLeafLdsPairs - kLeafLdsPairs / 4;
 constexpr int kNumProfiled = 6;  // timed stages: walk, plan, bucketing, leaf kernel, voxel combine, commit
 constexpr int kAccFrames = 8;        // frames of a pass the accumulating leaf kernel takes
 constexpr int kAccWavePairs = 128;   // accumulated leaves with at most this many pairs are one wave's work
@@ -196,11 +200,12 @@ struct MapDev {
     uint32_t *pair_key;   // leaf-kernel scratch: sorted keys of bins beyond LDS, wave-combine input
     float *pair_tsdf;     // and their truncated distances
     uint2 *srt_kv;        // pairs grouped by leaf: (key, truncated distance bits)
-    int32_t *srt_lab;     // int32 label of each bucketed pair (closed set with labels)
+    int32_t *srt_lab;     // accumulated frames: int32 label of each bucketed pair; binned frames: 512 bin
+                          // starts at the bucket of each large leaf
     uint32_t *tmp_key;    // scratch of large leaves: pairs binned by voxel offset
     float *tmp_tsdf;
     uint32_t pair_cap;
-    int2 *work;           // slab work items (index in items_big, slab) of large leaves
+    int2 *work;           // work items (index in items_big, slab or range) of large leaves
     uint32_t work_cap;
     uint4 *vox_list;      // wave-combine voxels: (record, pairs | existed << 31, first sorted pair, 0)
     uint2 *blk_stats;     // per leaf-kernel block: (voxels updated that existed, voxels created)
@@ -209,6 +214,10 @@ struct MapDev {
     // one wave's work, sorted leaves with more than slab_pairs pairs are split
     // into x-slab items (0: the largest the kernels hold)
     int wave_pairs, slab_pairs;
+    // nonzero: the pairs of a sorted leaf beyond slab_pairs are binned by voxel
+    // offset before the leaf kernel (k_leaf_count, k_leaf_bin) and its work items
+    // are ranges of kRangePairs binned pairs instead of x-slabs
+    int binned;
     DevState *st;
     FrameState *fs;       // the staging buffer's frame counters
     long long max_leaves, max_pages;

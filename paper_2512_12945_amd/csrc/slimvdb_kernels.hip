@@ -662,7 +662,7 @@ __device__ __forceinline__ void leaf_plan_range(const FrameParams &fp, const Map
             need = md.pos_slab[pos] & ~have & 0xFFu;
         }
         // a leaf with more pairs than the leaf kernel holds in LDS becomes one
-        // work item per touched x-slab
+        // work item per touched x-slab, or per range of its binned pairs
         const uint32_t tslabs = act ? md.pos_slab[pos] & 0xFFu : 0u;
         const bool big = act && npairs > big_lim;
         // the other leaves: one workgroup each, or one wave each if small
@@ -672,10 +672,13 @@ __device__ __forceinline__ void leaf_plan_range(const FrameParams &fp, const Map
         // their arrays, the smaller ones from the back
         const bool medf = med && npairs > min(big_lim, slab_cap) / 2, medb = med && !medf;
         const bool smallf = small && npairs > small_lim / 4, smallb = small && !smallf;
+        const uint32_t nparts = !big ? 0u
+                                : md.binned ? (npairs + (uint32_t)kRangePairs - 1u) / (uint32_t)kRangePairs
+                                            : (uint32_t)__popc(tslabs);
         // eight reservations with six atomics in flight together (two list
         // counters share each 64-bit word)
         const uint32_t want[4] = {(act && slot < 0) ? 1u : 0u, (uint32_t)__popc(need), npairs,
-                                  big ? (uint32_t)__popc(tslabs) : 0u};
+                                  nparts};
         uint32_t incl[4], total[4], base[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -707,18 +710,18 @@ __device__ __forceinline__ void leaf_plan_range(const FrameParams &fp, const Map
         if (medb) dst = &md.items[last - ((uint32_t)lbb + mincb - 1u)];
         if (smallb) dst = &md.items_small[last - ((uint32_t)(lbb >> 32) + sincb - 1u)];
         if (big) {
-            // the leaf's slab items sit at ibase .. ibase + slabs - 1, its item at
+            // the leaf's work items sit at ibase .. ibase + nparts - 1, its item at
             // ibase; every work entry below work_cap is written, so the leaf
             // kernel never reads an unwritten one (a frame that overflows the
             // work list is not applied)
             if (ibase < md.work_cap) dst = &md.items_big[ibase];
-            uint32_t r = 0;
-            for (int q = 0; q < kLeafPages; ++q)
-                if ((tslabs >> q) & 1u) {
-                    if (ibase + r < md.work_cap) md.work[ibase + r] = make_int2((int)ibase, q);
-                    else atomicOr(&md.fs->frame_err.v, 1u);
-                    r++;
-                }
+            uint32_t left = tslabs;
+            for (uint32_t r = 0; r < nparts; ++r) {
+                const int part = md.binned ? (int)r : __ffs(left) - 1;
+                left &= left - 1u;
+                if (ibase + r < md.work_cap) md.work[ibase + r] = make_int2((int)ibase, part);
+                else atomicOr(&md.fs->frame_err.v, 1u);
+            }
         }
         if (act) {
             uint32_t r = 0;
@@ -762,7 +765,7 @@ __device__ __forceinline__ void pair_bucket_range(const FrameParams &fp, const M
 {
     const uint32_t P = min(md.fs->pairs.v, md.pair_cap);
     const uint32_t stride = nblk * blockDim.x;
-    const bool labels = fp.K > 0 && fp.sem_kind == SLIM_IN_LABEL_I32;
+    const bool labels = fp.K > 0 && accum_path(fp);  // (the sorting leaf kernels read labels by point index)
     // four pairs per thread and round, each step's loads issued together
     constexpr int U = 4;
     for (uint32_t i0 = blk * blockDim.x + threadIdx.x; i0 < P; i0 += U * stride) {
@@ -799,6 +802,96 @@ __global__ __launch_bounds__(256) void k_pair_bucket_batch(MapBatch mb)
     const int i = batch_map(mb.bucket_first, mb.nmaps, blockIdx.x);
     pair_bucket_range(mb.fps[i], mb.mds[i], blockIdx.x - mb.bucket_first[i],
                       mb.bucket_first[i + 1] - mb.bucket_first[i]);
+}
+
+// ---------------------------------------------------------------------------
+// 3'. binning of large leaves
+// ---------------------------------------------------------------------------
+//
+// A leaf with more pairs than the sorting leaf kernel holds in LDS is shared by
+// several workgroups.  Without binning each of them takes an x-slab and reads
+// every pair of the leaf to find its own, twice when they are many: at 640x480
+// pixels and 2 cm voxels the 206 leaves touched hold up to 61,000 pairs, and
+// those reads were most of the leaf kernel's time.  These two kernels group the
+// pairs by voxel offset first, a workgroup per range of kRangePairs bucketed
+// pairs: k_leaf_count counts each range's offsets, k_leaf_bin forms the leaf's
+// bin starts from its ranges' counts (no atomics between workgroups) and moves
+// the range's pairs to their bins.  The leaf kernel's items are then ranges of
+// whole bins of about that many pairs, each reading its own pairs once.
+// Bound by the pairs' bytes (8 read twice, 8 written); the order inside a bin is
+// arbitrary, as it is without binning.  That frame: leaf kernel 532 -> 65 us, these
+// two kernels 9 and 18 us.
+
+// 16-bit counts of range u's offsets, two to a word, in the sorted keys' buffer
+// (free until the leaf kernel).  A large leaf has more than 512 pairs, so the
+// ranges are at most pairs / 1536 + pairs / 512 and their 1 KB rows fit.
+constexpr int kRangeBatch = kRangePairs / 256;
+__device__ __forceinline__ uint32_t *range_counts(const MapDev &md, uint32_t u) { return md.pair_key + (size_t)u * 256; }
+
+__global__ __launch_bounds__(256) void k_leaf_count(MapDev md)
+{
+    __shared__ uint32_t hist[kLeafVoxels];
+    const uint32_t nbig = min(md.fs->work_big.v, md.work_cap), tid = threadIdx.x;
+    for (uint32_t u = blockIdx.x; u < nbig; u += gridDim.x) {
+        const int2 it = md.work[u];
+        const LeafItem &item = md.items_big[it.x];
+        const uint32_t t0 = (uint32_t)it.y * kRangePairs, n = min(item.n - t0, (uint32_t)kRangePairs);
+        const uint2 *kv = md.srt_kv + item.bstart + t0;
+        hist[tid] = 0u;
+        hist[tid + 256] = 0u;
+        uint32_t key[kRangeBatch];
+#pragma unroll
+        for (int q = 0; q < kRangeBatch; ++q) key[q] = q * 256 + tid < n ? kv[q * 256 + tid].x : 0u;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kRangeBatch; ++q)
+            if (q * 256 + tid < n) atomicAdd(&hist[key[q] >> kPidBits], 1u);
+        __syncthreads();
+        range_counts(md, u)[tid] = hist[2 * tid] | (hist[2 * tid + 1] << 16);
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(256) void k_leaf_bin(MapDev md)
+{
+    __shared__ uint32_t cur[kLeafVoxels], wsum[4];
+    const uint32_t nbig = min(md.fs->work_big.v, md.work_cap), tid = threadIdx.x;
+    for (uint32_t u = blockIdx.x; u < nbig; u += gridDim.x) {
+        const int2 it = md.work[u];
+        const LeafItem &item = md.items_big[it.x];
+        const uint32_t c = (uint32_t)it.y, t0 = c * kRangePairs, n = min(item.n - t0, (uint32_t)kRangePairs);
+        const uint32_t nranges = (item.n + kRangePairs - 1) / kRangePairs;
+        const uint2 *kv = md.srt_kv + item.bstart + t0;
+        uint2 e[kRangeBatch];
+#pragma unroll
+        for (int q = 0; q < kRangeBatch; ++q) e[q] = q * 256 + tid < n ? kv[q * 256 + tid] : make_uint2(0u, 0u);
+        // offsets 2 tid and 2 tid + 1: their pairs in the leaf, and in the ranges before this one
+        uint32_t a = 0, b = 0, a0 = 0, b0 = 0;
+#pragma unroll 8
+        for (uint32_t r = 0; r < nranges; ++r) {
+            const uint32_t w = range_counts(md, (uint32_t)it.x + r)[tid];
+            if (r == c) {
+                a0 = a;
+                b0 = b;
+            }
+            a += w & 0xFFFFu;
+            b += w >> 16;
+        }
+        uint32_t total;
+        const uint32_t start = block_excl_scan(a + b, wsum, &total);
+        if (c == 0) ((uint2 *)(md.srt_lab + item.bstart + (item.bstart & 1u)))[tid] = make_uint2(start, start + a);
+        cur[2 * tid] = start + a0;
+        cur[2 * tid + 1] = start + a + b0;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kRangeBatch; ++q)
+            if (q * 256 + tid < n) {
+                const uint32_t p = item.bstart + atomicAdd(&cur[e[q].x >> kPidBits], 1u);
+                md.tmp_key[p] = e[q].x;
+                md.tmp_tsdf[p] = __uint_as_float(e[q].y);
+            }
+        __syncthreads();
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1486,16 +1579,18 @@ __device__ __forceinline__ void rank_bins(LeafShared &sh, KP bk, VP bv, uint32_t
 }
 
 // One work item of the leaf kernel: the touched leaf of item *itp, all
-// of it (slab < 0) or, for a leaf with more pairs than LDS holds, the voxels
-// of one x-slab (offsets 64 slab .. 64 slab + 63), so that the slabs of a
-// large leaf run in different workgroups.  Reads every pair of the leaf for
-// the offset histogram (which fixes the bucket position of every voxel),
-// keeps those of its offsets, orders them by point index inside each voxel and
-// combines the voxels.  An x-slab item reads the leaf once when its own pairs
-// fit LDS and a second time otherwise.
+// of it (part < 0) or, for a leaf with more pairs than LDS holds, one part of
+// it, so that the parts of a large leaf run in different workgroups.  The part
+// is an x-slab (offsets 64 part .. 64 part + 63): the item then reads every
+// pair of the leaf for the offset histogram (which fixes the bucket position of
+// every voxel) and keeps those of its offsets, reading the leaf once when they
+// fit LDS and a second time otherwise.  In a binned frame the part is the
+// voxels whose bins start in pairs kRangePairs part + [0, kRangePairs): bin
+// starts and binned pairs are there already.  The item orders its pairs by point
+// index inside each voxel and combines the voxels.
 template <int KMAX, bool WAVE, bool ROWS>
 __device__ __forceinline__ void fuse_item(const FrameParams &fp, const MapDev &md, LeafShared &sh, LeafItem *itp,
-                                          int slab, unsigned long long lused, bool ok)
+                                          int part, unsigned long long lused, bool ok)
 {
     const int tid = threadIdx.x;
     if (tid < 32) sh.item[tid] = ((const uint32_t *)itp)[tid];
@@ -1505,10 +1600,11 @@ __device__ __forceinline__ void fuse_item(const FrameParams &fp, const MapDev &m
     const uint32_t pos = sh.item[0], n = sh.item[1], bstart = sh.item[2];
     const int islot = (int)sh.item[3];
     const int slot = islot >= 0 ? islot : (int)(lused + (unsigned long long)(-1 - islot));
-    const uint32_t ob = slab < 0 ? 0u : 64u * (uint32_t)slab, oe = slab < 0 ? (uint32_t)kLeafVoxels : ob + 64u;
-    // a new leaf is inserted by the item of its lowest touched slab (or its
-    // whole-leaf item); the first probe goes out with the pair loads
-    const bool lead = slab < 0 || (uint32_t)slab == (uint32_t)(__ffs(sh.item[4] & 0xFFu) - 1);
+    const bool binned = part >= 0 && md.binned;
+    uint32_t ob = part < 0 ? 0u : 64u * (uint32_t)part, oe = part < 0 ? (uint32_t)kLeafVoxels : ob + 64u;
+    // a new leaf is inserted by its whole-leaf item, the item of its lowest
+    // touched slab or of its first range; the first probe goes out with the pair loads
+    const bool lead = part < 0 || part == (binned ? 0 : __ffs(sh.item[4] & 0xFFu) - 1);
     const bool inserts = ok && lead && islot < 0 && tid == 0;
     const unsigned long long lkey = ((unsigned long long)sh.item[7] << 32) | sh.item[6];
     uint32_t ih = 0;
@@ -1520,13 +1616,32 @@ __device__ __forceinline__ void fuse_item(const FrameParams &fp, const MapDev &m
     const uint2 *gkv = md.srt_kv + bstart;
     uint32_t *tk = md.tmp_key + bstart;
     float *tv = md.tmp_tsdf + bstart;
-    const bool whole_small = slab < 0 && n <= (uint32_t)kLeafLdsPairs;
+    const bool whole_small = part < 0 && n <= (uint32_t)kLeafLdsPairs;
 
     // histogram of the voxel offsets of every pair of the leaf; kLeafBatch loads
     // in flight per thread, and a whole leaf that fits LDS stays in registers
     uint32_t rk[kLeafBatch];
     float rv[kLeafBatch];
-    if (whole_small) {
+    if (binned) {
+        const uint2 s2 = ((const uint2 *)(md.srt_lab + bstart + (bstart & 1u)))[tid];
+        sh.bin0[2 * tid] = s2.x;
+        sh.bin0[2 * tid + 1] = s2.y;
+        __syncthreads();
+        sh.hist[2 * tid] = s2.y - s2.x;
+        sh.hist[2 * tid + 1] = (tid < 255 ? sh.bin0[2 * tid + 2] : n) - s2.y;
+        // first offsets whose bins start at or after the range's ends
+        auto first = [&](uint32_t lim) {
+            uint32_t lo = 0, hi = kLeafVoxels;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (sh.bin0[mid] < lim) lo = mid + 1;
+                else hi = mid;
+            }
+            return lo;
+        };
+        ob = first((uint32_t)part * kRangePairs);
+        oe = first(((uint32_t)part + 1u) * kRangePairs);
+    } else if (whole_small) {
 #pragma unroll
         for (int u = 0; u < kLeafBatch; ++u) {
             const uint32_t t = u * kLeafThreads + tid;
@@ -1576,8 +1691,10 @@ __device__ __forceinline__ void fuse_item(const FrameParams &fp, const MapDev &m
         }
     }
     __syncthreads();
-    block_scan512(sh.hist, sh.bin0, sh.wsum);
-    for (int o = tid; o < kLeafVoxels; o += blockDim.x) sh.cur[o] = sh.bin0[o];
+    if (!binned) {
+        block_scan512(sh.hist, sh.bin0, sh.wsum);
+        for (int o = tid; o < kLeafVoxels; o += blockDim.x) sh.cur[o] = sh.bin0[o];
+    }
     {
         // touched offsets: wave w covers bins 64w + [0, 64) and 256 + 64w + [0, 64)
         const int w = tid >> 6;
@@ -1615,13 +1732,15 @@ __device__ __forceinline__ void fuse_item(const FrameParams &fp, const MapDev &m
             md.vox_list[vbase + r] = make_uint4(rec, n_o | (existed << 31), bstart + sh.bin0[o], 0u);
         }
     }
-    const uint32_t lo_all = sh.bin0[ob], hi_all = oe < (uint32_t)kLeafVoxels ? sh.bin0[oe] : n;
-    const bool small = whole_small || (slab >= 0 && hi_all - lo_all <= (uint32_t)kLeafLdsPairs);
+    const uint32_t lo_all = ob < (uint32_t)kLeafVoxels ? sh.bin0[ob] : n;
+    const uint32_t hi_all = oe < (uint32_t)kLeafVoxels ? sh.bin0[oe] : n;
+    const bool small = whole_small || (part >= 0 && hi_all - lo_all <= (uint32_t)kLeafLdsPairs);
     if (tid == 0) {
         uint32_t uo = 0, un = 0;
-        for (uint32_t w = ob >> 5; w < (oe >> 5); ++w) {
-            uo += __popc(sh.touch[w] & sh.occ0[w]);
-            un += __popc(sh.touch[w] & ~sh.occ0[w]);
+        for (uint32_t w = ob >> 5; w < (oe + 31u) >> 5; ++w) {
+            const uint32_t mine = range_bits(sh.touch[w], w, ob, oe);
+            uo += __popc(mine & sh.occ0[w]);
+            un += __popc(mine & ~sh.occ0[w]);
         }
         sh.uold += uo;
         sh.unew += un;
@@ -1638,6 +1757,12 @@ __device__ __forceinline__ void fuse_item(const FrameParams &fp, const MapDev &m
                 const uint32_t p = atomicAdd(&sh.cur[rk[u] >> kPidBits], 1u);
                 sh.b_key[p] = rk[u];
                 sh.b_val[p] = rv[u];
+            }
+    } else if (binned) {
+        if (small)
+            for (uint32_t t = tid; t < hi_all - lo_all; t += blockDim.x) {
+                sh.b_key[t] = tk[lo_all + t];
+                sh.b_val[t] = tv[lo_all + t];
             }
     } else if (small) {
         const uint32_t m = hi_all - lo_all;
@@ -1734,9 +1859,11 @@ __device__ __forceinline__ void fuse_item(const FrameParams &fp, const MapDev &m
         o0 = o1;
     }
 
-    // leaf bookkeeping: an item owns the page entry and the occupancy words of
-    // its offsets; the item of the leaf's lowest touched slab (or the whole-leaf
-    // item) also inserts a new leaf and writes the entries of untouched slabs
+    // leaf bookkeeping: an x-slab item owns the page entry and the occupancy
+    // words of its offsets; the item of the leaf's lowest touched slab also
+    // inserts a new leaf and writes the entries of untouched slabs.  The
+    // whole-leaf item, or the item of the first range (every item of a binned
+    // leaf has the whole leaf's counts), does all of it
     if (ok) {
         const uint32_t tslabs = sh.item[4] & 0xFFu;
         if (inserts) {
@@ -1744,21 +1871,23 @@ __device__ __forceinline__ void fuse_item(const FrameParams &fp, const MapDev &m
             md.leaf_key[slot] = lkey;
         }
         if (tid < kLeafPages) {
-            const bool mine = slab < 0 || tid == slab || (lead && !((tslabs >> tid) & 1u));
+            const bool mine = part < 0 || binned ? lead : tid == part || (lead && !((tslabs >> tid) & 1u));
             if (mine) md.leaf_page[(size_t)slot * kLeafPages + tid] = sh.pages[tid];
         }
         if (tid < kMaskWords) {
             const int sl = tid >> 1;
-            const bool mine = slab < 0 || sl == slab || (lead && !((tslabs >> sl) & 1u));
+            const bool mine = part < 0 || binned ? lead : sl == part || (lead && !((tslabs >> sl) & 1u));
             if (mine) md.leaf_occ[(size_t)slot * kMaskWords + tid] = sh.occ0[tid] | sh.touch[tid];
         }
     }
     __syncthreads();
     if (tid == 0) {
         // the staging entry is clean for the next frame once the leaf's last
-        // item is done (a whole-leaf item is the only one; slab items count
-        // themselves in the item's spare word, which the plan kernel zeroes)
-        const bool last = slab < 0 || atomicAdd(&itp->pad, 1u) + 1u == (uint32_t)__popc(sh.item[4] & 0xFFu);
+        // item is done (a whole-leaf item is the only one; the parts of a large
+        // leaf count themselves in the item's spare word, which the plan kernel zeroes)
+        const uint32_t nparts = binned ? (n + (uint32_t)kRangePairs - 1u) / (uint32_t)kRangePairs
+                                       : (uint32_t)__popc(sh.item[4] & 0xFFu);
+        const bool last = part < 0 || atomicAdd(&itp->pad, 1u) + 1u == nparts;
         if (last) {
             md.skeys[pos] = kEmptyKey;
             md.pos_count[pos] = 0u;
@@ -2960,10 +3089,31 @@ static void launch_leaf_batch(int kind, const MapBatch &mb, int blocks, hipStrea
     }
 }
 
+// Frames whose large leaves are binned.  The two launches cost about 10 us and
+// save what the x-slab items read more than once, which grows with the square of
+// the points per leaf: at 33,127 pixels (L = 100) the leaf stage takes 29 us with
+// slabs and 27 us binned, at 65,536 LiDAR rays with class rows 103 and 111 us, at
+// 131,071 rays 262 and 222 us, at 307,200 pixels (L = 512) 544 and 104 us.
+constexpr int kBinPoints = 65536;
+
+static bool bins_large_leaves(const FrameParams &fp) { return !accum_path(fp) && fp.n > kBinPoints; }
+
+static void launch_bucket(const FrameParams &fp, const MapDev &md, const LaunchShape &shape, hipStream_t s)
+{
+    const long long want = ((long long)fp.n * fp.maxsteps + 255) / 256;
+    const int bb = (int)std::max<long long>(1, std::min<long long>(want, shape.bucket_blocks));
+    hipLaunchKernelGGL(k_pair_bucket, dim3(bb), dim3(256), 0, s, fp, md);
+    if (md.binned) {
+        hipLaunchKernelGGL(k_leaf_count, dim3(4 * shape.cus), dim3(256), 0, s, md);
+        hipLaunchKernelGGL(k_leaf_bin, dim3(4 * shape.cus), dim3(256), 0, s, md);
+    }
+}
+
 hipError_t launch_integrate(const FrameParams &fp, const MapDev &md_in, const LaunchShape &shape, hipStream_t s,
                             hipEvent_t *ev, const PassWalk *pw)
 {
     MapDev md = md_in;
+    md.binned = bins_large_leaves(fp) ? 1 : 0;
     md.leaf_blocks = shape.leaf_blocks;
     md.wave_pairs = shape.wave_pairs;
     md.slab_pairs = shape.slab_pairs;
@@ -2983,9 +3133,7 @@ hipError_t launch_integrate(const FrameParams &fp, const MapDev &md_in, const La
     hipLaunchKernelGGL(k_leaf_plan, dim3(shape.plan_blocks), dim3(256), 0, s, fp, md);
     rec(3);
     rec(4);
-    const long long want = ((long long)fp.n * fp.maxsteps + 255) / 256;
-    const int bb = (int)std::max<long long>(1, std::min<long long>(want, shape.bucket_blocks));
-    hipLaunchKernelGGL(k_pair_bucket, dim3(bb), dim3(256), 0, s, fp, md);
+    launch_bucket(fp, md, shape, s);
     rec(5);
     rec(6);
     const int kind = leaf_kernel_kind(fp);
@@ -3015,13 +3163,12 @@ hipError_t launch_walk(const FrameParams &fp, const MapDev &md, hipStream_t s, c
 hipError_t launch_after_walk(const FrameParams &fp, const MapDev &md_in, const LaunchShape &shape, hipStream_t s)
 {
     MapDev md = md_in;
+    md.binned = bins_large_leaves(fp) ? 1 : 0;
     md.leaf_blocks = shape.leaf_blocks;
     md.wave_pairs = shape.wave_pairs;
     md.slab_pairs = shape.slab_pairs;
     hipLaunchKernelGGL(k_leaf_plan, dim3(shape.plan_blocks), dim3(256), 0, s, fp, md);
-    const long long want = ((long long)fp.n * fp.maxsteps + 255) / 256;
-    const int bb = (int)std::max<long long>(1, std::min<long long>(want, shape.bucket_blocks));
-    hipLaunchKernelGGL(k_pair_bucket, dim3(bb), dim3(256), 0, s, fp, md);
+    launch_bucket(fp, md, shape, s);
     const int kind = leaf_kernel_kind(fp);
     launch_leaf(kind, fp, md, shape.leaf_blocks, s);
     launch_voxel_combine(kind, fp, md, combine_blocks(kind, shape), s);

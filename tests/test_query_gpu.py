@@ -9,7 +9,7 @@ import torch
 
 from paper_2512_12945_amd import slimvdb as sv
 from paper_2512_12945_amd import synth
-from tests._gpu_util import cuda
+from _gpu_util import cuda
 
 pytestmark = pytest.mark.gpu
 
