@@ -760,6 +760,48 @@ __global__ __launch_bounds__(256) void k_leaf_plan_batch(MapBatch mb)
 // 3. pair bucketing
 // ---------------------------------------------------------------------------
 
+// Softmax of every point's logits (max-subtracted), one lane per point, into rows
+// of soft_stride(K) floats (padded with zeros) in the wave combine's descriptor
+// buffer, which frames of class rows do not use (16 bytes x at least 10 cells per
+// point hold 32 classes).  Formed here once per point, an observation costs the
+// combine one row of additions; formed there, once per observation (9 per point),
+// its exponentials and divisions bound the leaf kernel.  65,536 rays, 20 classes:
+// leaf kernel 96 -> 43 us (vector rows included), bucketing 7 -> 11 us; 131,071 rays:
+// 200 -> 65 us, 9 -> 16 us.
+__host__ __device__ inline int soft_stride(int K) { return (K + 3) & ~3; }
+
+__host__ __device__ inline bool soft_rows(const FrameParams &fp)
+{
+    return fp.sem_kind == SLIM_IN_LOGIT_F32 && !fp.last && fp.K <= 32;
+}
+
+__device__ __forceinline__ void softmax_rows_range(const FrameParams &fp, const MapDev &md, uint32_t blk, uint32_t nblk)
+{
+    constexpr int KMAX = 32;
+    const int K = fp.K, stride = soft_stride(K);
+    for (uint32_t i = blk * blockDim.x + threadIdx.x; i < (uint32_t)fp.n; i += nblk * blockDim.x) {
+        const float *row = (const float *)fp.sem + (size_t)i * K;
+        float4 *out = (float4 *)((float *)md.vox_list + (size_t)i * stride);
+        float x[KMAX];
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) x[k] = k < K ? row[k] : 0.0f;
+        float mx = x[0];
+#pragma unroll
+        for (int k = 1; k < KMAX; ++k)
+            if (k < K) mx = fmaxf(mx, x[k]);
+        float den = 0.0f;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k)
+            if (k < K) {
+                x[k] = expf(x[k] - mx);
+                den += x[k];
+            }
+#pragma unroll
+        for (int v = 0; v < KMAX / 4; ++v)
+            if (4 * v < K) out[v] = make_float4(x[4 * v] / den, x[4 * v + 1] / den, x[4 * v + 2] / den, x[4 * v + 3] / den);
+    }
+}
+
 __device__ __forceinline__ void pair_bucket_range(const FrameParams &fp, const MapDev &md, uint32_t blk,
                                                   uint32_t nblk)
 {
@@ -792,16 +834,20 @@ __device__ __forceinline__ void pair_bucket_range(const FrameParams &fp, const M
     }
 }
 
+// SOFT: frames of logit rows (apart, so that the others keep their registers)
+template <bool SOFT>
 __global__ __launch_bounds__(256) void k_pair_bucket(FrameParams fp, MapDev md)
 {
+    if constexpr (SOFT) softmax_rows_range(fp, md, blockIdx.x, gridDim.x);
     pair_bucket_range(fp, md, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(256) void k_pair_bucket_batch(MapBatch mb)
 {
     const int i = batch_map(mb.bucket_first, mb.nmaps, blockIdx.x);
-    pair_bucket_range(mb.fps[i], mb.mds[i], blockIdx.x - mb.bucket_first[i],
-                      mb.bucket_first[i + 1] - mb.bucket_first[i]);
+    const uint32_t blk = blockIdx.x - mb.bucket_first[i], nblk = mb.bucket_first[i + 1] - mb.bucket_first[i];
+    if (soft_rows(mb.fps[i])) softmax_rows_range(mb.fps[i], mb.mds[i], blk, nblk);
+    pair_bucket_range(mb.fps[i], mb.mds[i], blk, nblk);
 }
 
 // ---------------------------------------------------------------------------
@@ -971,15 +1017,21 @@ __device__ __forceinline__ float tsdf_mean(float D0, float W0, float W1, long lo
 }
 
 // One voxel, one lane: its n observations sit at keys[0..n) / vals[0..n) in
-// point order.  Closed set with probability or logit rows and K <= KMAX
-// classes in registers.  The record moves as 16-byte vectors.
+// point order.  Closed set with probability rows (or the softmax of logit rows,
+// formed once per point by softmax_rows_range) and K <= KMAX classes in
+// registers.  Rows (16-byte aligned ones) and the record move as 16-byte
+// vectors.
 template <int KMAX>
 __device__ __forceinline__ void combine_lane(const FrameParams &fp, const MapDev &md, const uint32_t *keys,
                                              const float *vals, uint32_t n, long long rec, bool existed)
 {
-    static_assert(KMAX > 0, "rows of at least one class");
+    static_assert(KMAX > 0 && KMAX % 4 == 0, "rows of at least one class, in whole vectors");
     constexpr int NV = (2 + KMAX + 3) / 4;
     const int nv = md.rec_stride / 4, K = fp.K;
+    const bool soft = fp.sem_kind == SLIM_IN_LOGIT_F32;
+    const float *rows = soft ? (const float *)md.vox_list : (const float *)fp.sem;
+    const int stride = soft ? soft_stride(K) : K;
+    const bool vec = (stride & 3) == 0 && ((uintptr_t)rows & 15u) == 0;
     // up to 16 classes the record is requested first, so its round trip
     // overlaps the rows (more would spill registers)
     constexpr bool early = KMAX <= 16;
@@ -999,40 +1051,39 @@ __device__ __forceinline__ void combine_lane(const FrameParams &fp, const MapDev
     float acc[KMAX];
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) acc[k] = 0.0f;
-    // the rows of RB observations are loaded before any is used (two up to 24
-    // classes; more would spill registers), then each is added in point order
+    // the rows of RB observations are loaded before any is used, then each is
+    // added in point order (four rows of 24 classes cost a third of the waves:
+    // 49 us against 43 with two at 65,536 rays)
     constexpr int RB = KMAX <= 24 ? 2 : 1;
     for (uint32_t t0 = 0; t0 < n; t0 += RB) {
         float x[RB][KMAX];
+        if (vec) {
 #pragma unroll
-        for (int b = 0; b < RB; ++b) {
-            const bool has = t0 + b < n;
-            const float *row = (const float *)fp.sem + (size_t)(has ? keys[t0 + b] & kPidMask : 0u) * K;
+            for (int b = 0; b < RB; ++b) {
+                const float4 *row = (const float4 *)(rows + (size_t)(keys[min(t0 + b, n - 1)] & kPidMask) * stride);
 #pragma unroll
-            for (int k = 0; k < KMAX; ++k) x[b][k] = (has && k < K) ? row[k] : 0.0f;
+                for (int v = 0; v < KMAX / 4; ++v) {
+                    const float4 q = 4 * v < K ? row[v] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    x[b][4 * v + 0] = q.x;
+                    x[b][4 * v + 1] = q.y;
+                    x[b][4 * v + 2] = q.z;
+                    x[b][4 * v + 3] = q.w;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+                const float *row = rows + (size_t)(keys[min(t0 + b, n - 1)] & kPidMask) * stride;
+#pragma unroll
+                for (int k = 0; k < KMAX; ++k) x[b][k] = k < K ? row[k] : 0.0f;
+            }
         }
 #pragma unroll
-        for (int b = 0; b < RB; ++b) {
+        for (int b = 0; b < RB; ++b)
             if (t0 + b < n) {
-                if (fp.sem_kind == SLIM_IN_LOGIT_F32) {
-                    // softmax of the logits, max-subtracted
-                    float mx = x[b][0];
-#pragma unroll
-                    for (int k = 1; k < KMAX; ++k)
-                        if (k < K) mx = fmaxf(mx, x[b][k]);
-                    float den = 0.0f;
-#pragma unroll
-                    for (int k = 0; k < KMAX; ++k) {
-                        x[b][k] = k < K ? expf(x[b][k] - mx) : 0.0f;
-                        den += x[b][k];
-                    }
-#pragma unroll
-                    for (int k = 0; k < KMAX; ++k) x[b][k] = x[b][k] / den;
-                }
 #pragma unroll
                 for (int k = 0; k < KMAX; ++k) acc[k] += x[b][k];
             }
-        }
     }
     if constexpr (!early) load_record();
     // Eq. (1)-(2) with unit weights
@@ -2814,6 +2865,7 @@ __device__ __noinline__ void persist_plan(const FrameParams &fp, const MapDev &m
 
 __device__ __noinline__ void persist_bucket(const FrameParams &fp, const MapDev &md, uint32_t j, uint32_t cnt)
 {
+    if (soft_rows(uni_ref(fp))) softmax_rows_range(uni_ref(fp), uni_ref(md), uni(j), uni(cnt));
     pair_bucket_range(uni_ref(fp), uni_ref(md), uni(j), uni(cnt));
 }
 
@@ -3102,7 +3154,8 @@ static void launch_bucket(const FrameParams &fp, const MapDev &md, const LaunchS
 {
     const long long want = ((long long)fp.n * fp.maxsteps + 255) / 256;
     const int bb = (int)std::max<long long>(1, std::min<long long>(want, shape.bucket_blocks));
-    hipLaunchKernelGGL(k_pair_bucket, dim3(bb), dim3(256), 0, s, fp, md);
+    if (soft_rows(fp)) hipLaunchKernelGGL(k_pair_bucket<true>, dim3(bb), dim3(256), 0, s, fp, md);
+    else hipLaunchKernelGGL(k_pair_bucket<false>, dim3(bb), dim3(256), 0, s, fp, md);
     if (md.binned) {
         hipLaunchKernelGGL(k_leaf_count, dim3(4 * shape.cus), dim3(256), 0, s, md);
         hipLaunchKernelGGL(k_leaf_bin, dim3(4 * shape.cus), dim3(256), 0, s, md);
