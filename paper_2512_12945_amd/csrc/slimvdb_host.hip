@@ -98,9 +98,7 @@ struct slim_map {
     hipEvent_t ev_in = nullptr, ev_free[2] = {nullptr, nullptr}, ev_walk[2] = {nullptr, nullptr};
     bool used[2] = {false, false};
     // extraction scratch
-    unsigned long long *ext_keys = nullptr;
-    int32_t *ext_slots = nullptr;
-    uint32_t *ext_offsets = nullptr;
+    ExtractScratch ext = {};
     size_t ext_cap = 0;
     // kernel timing
     bool prof = false;
@@ -778,23 +776,22 @@ slim_status slim_extract(slim_map *m, int64_t capacity, int32_t *keys, float *d,
     hipStream_t s = (hipStream_t)stream;
     if ((size_t)st.leaves > m->ext_cap) {
         HIP_OK(hipStreamSynchronize(s));
-        for (void *p : {(void *)m->ext_keys, (void *)m->ext_slots, (void *)m->ext_offsets}) {
+        for (void *p : {(void *)m->ext.keys, (void *)m->ext.keys2, (void *)m->ext.slots, (void *)m->ext.slots2,
+                        (void *)m->ext.offsets}) {
             if (!p) continue;
             (void)hipFree(p);
             m->allocs.erase(std::remove(m->allocs.begin(), m->allocs.end(), p), m->allocs.end());
         }
-        m->ext_keys = nullptr;
-        m->ext_slots = nullptr;
-        m->ext_offsets = nullptr;
+        m->ext = {};
         m->ext_cap = 0;
         const size_t cap = (size_t)st.leaves;
-        if ((r = dalloc(m, &m->ext_keys, cap)) || (r = dalloc(m, &m->ext_slots, cap)) ||
-            (r = dalloc(m, &m->ext_offsets, cap)))
+        if ((r = dalloc(m, &m->ext.keys, cap)) || (r = dalloc(m, &m->ext.keys2, cap)) ||
+            (r = dalloc(m, &m->ext.slots, cap)) || (r = dalloc(m, &m->ext.slots2, cap)) ||
+            (r = dalloc(m, &m->ext.offsets, cap)))
             return r;
         m->ext_cap = cap;
     }
-    HIP_OK(launch_extract(m->md, m->nsem, st.leaves, m->ext_keys, m->ext_slots, m->ext_offsets, keys, d, w,
-                          m->nsem ? sem : nullptr, s));
+    HIP_OK(launch_extract(m->md, m->nsem, st.leaves, m->ext, keys, d, w, m->nsem ? sem : nullptr, s));
     HIP_OK(hipStreamSynchronize(s));
     return SLIM_OK;
 }
@@ -823,12 +820,15 @@ slim_status slim_extract_noalloc(slim_map *m, int64_t capacity, int32_t *keys, f
     if (!ptr) return fail(SLIM_ERR_DEVICE, "scratch address of device %d unavailable", m->cfg.device);
     DeviceGuard g(m->cfg.device);
     hipStream_t s = (hipStream_t)stream;
-    // keys, slots and offsets of the leaves, each array sized for the maximum;
-    // every entry the kernels read is written first by this call
-    unsigned long long *tk = (unsigned long long *)ptr;
-    int32_t *ts = (int32_t *)(tk + kNoAllocMaxLeaves);
-    uint32_t *to = (uint32_t *)(ts + kNoAllocMaxLeaves);
-    HIP_OK(launch_extract(m->md, m->nsem, st.leaves, tk, ts, to, keys, d, w, m->nsem ? sem : nullptr, s));
+    // each array sized for the maximum; every entry the kernels read is written
+    // first by this call
+    ExtractScratch x;
+    x.keys = (unsigned long long *)ptr;
+    x.keys2 = x.keys + kNoAllocMaxLeaves;
+    x.slots = (int32_t *)(x.keys2 + kNoAllocMaxLeaves);
+    x.slots2 = x.slots + kNoAllocMaxLeaves;
+    x.offsets = (uint32_t *)(x.slots2 + kNoAllocMaxLeaves);
+    HIP_OK(launch_extract(m->md, m->nsem, st.leaves, x, keys, d, w, m->nsem ? sem : nullptr, s));
     HIP_OK(hipStreamSynchronize(s));
     return SLIM_OK;
 }
