@@ -134,7 +134,7 @@ struct LossParams {
     float alpha0;
     float *loss;             // 3 floats: total, cross-entropy term, L1 term
     float *adj;              // per record: K adjoints dL/dc, then dL/dD (stride adj_stride)
-    int32_t *adj_cnt;        // per record: surface samples in the voxel
+    int32_t *adj_cnt;        // per record: surface samples in the voxel, and whether it has a row of adjoints
     int adj_stride;
     float *part;             // block partial sums
     int32_t *part_cnt;       // block partial sample counts

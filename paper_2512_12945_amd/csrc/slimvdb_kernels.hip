@@ -3288,19 +3288,18 @@ __device__ __forceinline__ float block_sum(float v, float *red)
     return r;
 }
 
-// Clears the sample counts and the adjoints of every record in use, so that a
-// voxel the loss does not list (or lists with a label outside [0, K)) carries
-// zero adjoints into the backward.
+// A record's word of adj_cnt: the surface samples in its voxel, and kAdjRow once
+// its row of adjoints has been written.  Only these words are cleared (4 bytes a
+// record instead of a row): a voxel that the loss does not list has no row and
+// carries zero adjoints into the backward.
+constexpr int kAdjRow = 1 << 30;
+
 __global__ __launch_bounds__(256) void k_loss_clear(MapDev md, LossParams lp)
 {
-    const size_t n = (size_t)md.st->pages_used * kPageVoxels;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += stride) lp.adj_cnt[i] = 0;
-    // adj_stride is a multiple of 4 floats
-    float4 *a4 = (float4 *)lp.adj;
-    const size_t n4 = n * (size_t)(lp.adj_stride / 4);
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n4; i += stride)
-        a4[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    // (records come in pages of 64)
+    const size_t n = (size_t)md.st->pages_used * (kPageVoxels / 4), stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += stride)
+        ((int4 *)lp.adj_cnt)[i] = make_int4(0, 0, 0, 0);
 }
 
 // Surface samples: per voxel count (integer, so order-free) and block partials
@@ -3327,60 +3326,104 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_samples(FrameParams fp, M
 }
 
 // Voxels: cross-entropy of the Dirichlet predictive (Eq. (7)) at the true class,
-// adjoints dL/dc and dL/dD, block partials of the cross-entropy.
+// adjoints dL/dc and dL/dD, block partials of the cross-entropy.  Bound by the
+// records read and the rows written, both as 16-byte vectors; the number of
+// samples in the map is summed by the whole workgroup (one thread did it before:
+// 591,000 voxels and 40 blocks of samples 220 -> @LV@ us).
 __global__ __launch_bounds__(kLossThreads) void k_loss_voxels(FrameParams fp, MapDev md, LossParams lp, int nsb)
 {
     __shared__ float red[kLossThreads];
     __shared__ int s_mp;
-    if (threadIdx.x == 0) {
-        int mp = 0;
-        for (int b = 0; b < nsb; ++b) mp += lp.part_cnt[b];
-        s_mp = mp;
+    if (threadIdx.x == 0) s_mp = 0;
+    const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    long long rec = -1;
+    int y = -1;
+    if (i < lp.m) {
+        rec = voxel_record(md, lp.keys[3 * i], lp.keys[3 * i + 1], lp.keys[3 * i + 2]);
+        y = lp.labels[i];
     }
+    int mp = 0;
+    for (int b = threadIdx.x; b < nsb; b += kLossThreads) mp += lp.part_cnt[b];
+    __syncthreads();
+    if (mp) atomicAdd(&s_mp, mp);
     __syncthreads();
     const float inv_m = 1.0f / (float)lp.m, inv_mp = s_mp > 0 ? 1.0f / (float)s_mp : 0.0f;
-    const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     const int K = fp.K;
     float ce = 0.0f;
-    if (i < lp.m) {
-        const long long rec = voxel_record(md, lp.keys[3 * i], lp.keys[3 * i + 1], lp.keys[3 * i + 2]);
-        const int y = lp.labels[i];
-        if (rec >= 0) {
-            const float *R = md.vox + (size_t)rec * md.rec_stride;
-            float *A = lp.adj + (size_t)rec * lp.adj_stride;
-            // a label outside [0, K) adds no cross-entropy term (dL/dc = 0);
-            // the voxel's surface samples still count
-            if (y >= 0 && y < K) {
-                float tot = (float)K * lp.alpha0;
-                for (int k = 0; k < K; ++k) tot += R[2 + k];
-                const float ay = lp.alpha0 + R[2 + y];
-                ce = -logf(ay / tot);
-                const float g = inv_m / tot;
-                for (int k = 0; k < K; ++k) A[k] = k == y ? g - inv_m / ay : g;
+    if (rec >= 0) {
+        const float4 *R = (const float4 *)(md.vox + (size_t)rec * md.rec_stride);
+        float4 *A = (float4 *)(lp.adj + (size_t)rec * lp.adj_stride);
+        // a label outside [0, K) adds no cross-entropy term (dL/dc = 0);
+        // the voxel's surface samples still count
+        const bool term = y >= 0 && y < K;
+        float tot = (float)K * lp.alpha0, cy = 0.0f, D = 0.0f;
+#pragma unroll 4
+        for (int v = 0; v < md.rec_stride / 4; ++v) {
+            const float4 q = R[v];
+            const float x[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = 4 * v + e - 2;
+                if (k == -2) D = x[e];
+                if (k >= 0 && k < K) {
+                    tot += x[e];
+                    cy = k == y ? x[e] : cy;
+                }
             }
-            const float D = R[0];
-            const float sg = D > 0.0f ? 1.0f : (D < 0.0f ? -1.0f : 0.0f);
-            A[K] = sg * (float)lp.adj_cnt[rec] * inv_mp;
         }
+        const float ay = lp.alpha0 + cy;
+        const float g = term ? inv_m / tot : 0.0f, gy = g - inv_m / ay;
+        if (term) ce = -logf(ay / tot);
+        const float sg = D > 0.0f ? 1.0f : (D < 0.0f ? -1.0f : 0.0f);
+        const int cnt = lp.adj_cnt[rec] & (kAdjRow - 1);
+        const float ad = sg * (float)cnt * inv_mp;
+        for (int v = 0; v < lp.adj_stride / 4; ++v) {
+            float x[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = 4 * v + e;
+                x[e] = k < K ? (term && k == y ? gy : g) : (k == K ? ad : 0.0f);
+            }
+            A[v] = make_float4(x[0], x[1], x[2], x[3]);
+        }
+        lp.adj_cnt[rec] = cnt | kAdjRow;
     }
     ce = block_sum(ce, red);
     if (threadIdx.x == 0) lp.part[nsb + blockIdx.x] = ce;
 }
 
-__global__ __launch_bounds__(256) void k_loss_final(LossParams lp, int nsb, int nvb)
+// Sums of the block partials, by one workgroup: each thread strides over them,
+// then a fixed tree, in binary64 (2,310 partials one after the other took 95 us,
+// this 5 us).
+__global__ __launch_bounds__(kLossThreads) void k_loss_final(LossParams lp, int nsb, int nvb)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    float l1 = 0.0f, ce = 0.0f;
+    __shared__ double s_l1[kLossThreads], s_ce[kLossThreads];
+    __shared__ int s_mp[kLossThreads];
+    const int t = threadIdx.x;
+    double l1 = 0.0, ce = 0.0;
     int mp = 0;
-    for (int b = 0; b < nsb; ++b) {
-        l1 += lp.part[b];
+    for (int b = t; b < nsb; b += kLossThreads) {
+        l1 += (double)lp.part[b];
         mp += lp.part_cnt[b];
     }
-    for (int b = 0; b < nvb; ++b) ce += lp.part[nsb + b];
-    const float t_ce = ce / (float)lp.m, t_l1 = mp > 0 ? l1 / (float)mp : 0.0f;
-    lp.loss[0] = t_ce + t_l1;
-    lp.loss[1] = t_ce;
-    lp.loss[2] = t_l1;
+    for (int b = t; b < nvb; b += kLossThreads) ce += (double)lp.part[nsb + b];
+    s_l1[t] = l1;
+    s_ce[t] = ce;
+    s_mp[t] = mp;
+    __syncthreads();
+    for (int d = kLossThreads / 2; d > 0; d >>= 1) {
+        if (t < d) {
+            s_l1[t] += s_l1[t + d];
+            s_ce[t] += s_ce[t + d];
+            s_mp[t] += s_mp[t + d];
+        }
+        __syncthreads();
+    }
+    if (t != 0) return;
+    const double t_ce = s_ce[0] / (double)lp.m, t_l1 = s_mp[0] > 0 ? s_l1[0] / (double)s_mp[0] : 0.0;
+    lp.loss[0] = (float)(t_ce + t_l1);
+    lp.loss[1] = (float)t_ce;
+    lp.loss[2] = (float)t_l1;
 }
 
 hipError_t launch_loss(const FrameParams &fp, const MapDev &md, const LossParams &lp, hipStream_t s)
@@ -3390,94 +3433,192 @@ hipError_t launch_loss(const FrameParams &fp, const MapDev &md, const LossParams
     hipLaunchKernelGGL(k_loss_clear, dim3(1024), dim3(256), 0, s, md, lp);
     if (nsb > 0) hipLaunchKernelGGL(k_loss_samples, dim3(nsb), dim3(kLossThreads), 0, s, fp, md, lp);
     if (nvb > 0) hipLaunchKernelGGL(k_loss_voxels, dim3(nvb), dim3(kLossThreads), 0, s, fp, md, lp, nsb);
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, s, lp, nsb, nvb);
+    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kLossThreads), 0, s, lp, nsb, nvb);
     return hipGetLastError();
 }
 
-// One lane per ray: recompute the band walk, gather the adjoints of the voxels
-// it observed, and chain them through the softmax and the clamp.
-template <int KMAX>
-__global__ __launch_bounds__(256) void k_backward_rays(FrameParams fp, MapDev md, LossParams lp,
-                                                       const float *grad_scale, float *grad_logits,
-                                                       float *grad_ranges)
+// Four lanes per ray: recompute the band walk, gather the adjoints of the voxels
+// it observed, and chain them through the softmax and the clamp.  Bound by the
+// latency of the gathers, so they are taken apart from the walk: the walk (all
+// four lanes, registers only) lists the ray's leaves and cells in LDS; the lanes
+// then look up the leaves side by side, then the cells' records, and then each
+// adds its 16-byte vectors of the rows, four cells in flight.  (One lane per
+// ray, which waited for the lookup, the page and the row of every cell in turn,
+// took 62 us for 65,536 rays and 20 classes; this takes @BW@ us.)
+// NVL: vectors of a row per lane; row vector v belongs to lane v mod 4.
+constexpr int kBackRays = 64;               // rays per workgroup
+constexpr int kBackCells = 3 * 12 + 4 + 1;  // cells of a ray (sdf_trunc <= 6 voxel_size), odd row stride
+
+template <int NVL>
+__global__ __launch_bounds__(4 * kBackRays) void k_backward_rays(FrameParams fp, MapDev md, LossParams lp,
+                                                                 const float *grad_scale, float *grad_logits,
+                                                                 float *grad_ranges)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= fp.n) return;
+    __shared__ unsigned long long s_key[kBackRays][kMaxRuns];
+    __shared__ int s_slot[kBackRays][kMaxRuns], s_cell[kBackRays][kBackCells];
+    const int sub = threadIdx.x & 3, ray = threadIdx.x >> 2;
+    const int i = blockIdx.x * kBackRays + ray;
     const int K = fp.K;
-    float G[KMAX];
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) G[k] = 0.0f;
-    float gr = 0.0f;
-    Ray ry;
-    float x, y, z;
-    load_point(fp, i, x, y, z);
-    bool valid = make_ray(fp, x, y, z, ry);
-    if (valid) {
-        bool inrange = true;
-        unsigned long long cur = kEmptyKey;
-        int slot = -1;
-        const bool started = band_walk(fp, ry, [&](int cx, int cy, int cz) {
-            const int kx = fp.a[0] + cx, ky = fp.a[1] + cy, kz = fp.a[2] + cz;
-            if (!(key_ok(kx) && key_ok(ky) && key_ok(kz))) {
-                inrange = false;
-                return;
-            }
-            const float sdf = cell_sdf(fp, ry, cx, cy, cz);
-            if (!(sdf > -fp.tau) || !inrange) return;
-            const unsigned long long lk = pack_leaf(kx >> 3, ky >> 3, kz >> 3);
-            if (lk != cur) {
-                cur = lk;
-                slot = map_find(md, lk);
-            }
-            if (slot < 0) return;
-            const int off = ((kx & 7) << 6) | ((ky & 7) << 3) | (kz & 7);
-            const int page = md.leaf_page[(size_t)slot * kLeafPages + (off >> 6)];
-            if (page < 0) return;  // not a voxel of this map (inputs differ from the integrated ones)
-            const long long rec = (long long)page * kPageVoxels + (off & (kPageVoxels - 1));
-            const float *A = lp.adj + (size_t)rec * lp.adj_stride;
-#pragma unroll
-            for (int k = 0; k < KMAX; ++k)
-                if (k < K) G[k] += A[k];
-            // a voxel no loss sample landed in has a zero adjoint (and may be an
-            // unobserved record of an observed slab, W = 0)
-            if (sdf < fp.tau && A[K] != 0.0f) gr += A[K] / md.vox[(size_t)rec * md.rec_stride + 1];
-        });
-        valid = started && inrange;
+    bool valid = false;
+    int ncell = 0, nrun = 0;
+    unsigned long long inner = 0ull;  // cells in front of the clamp
+    if (i < fp.n) {
+        Ray ry;
+        float x, y, z;
+        load_point(fp, i, x, y, z);
+        if (make_ray(fp, x, y, z, ry)) {
+            bool inrange = true;
+            unsigned long long cur = kEmptyKey;
+            const bool started = band_walk(fp, ry, [&](int cx, int cy, int cz) {
+                const int kx = fp.a[0] + cx, ky = fp.a[1] + cy, kz = fp.a[2] + cz;
+                if (!(key_ok(kx) && key_ok(ky) && key_ok(kz))) {
+                    inrange = false;
+                    return;
+                }
+                const float sdf = cell_sdf(fp, ry, cx, cy, cz);
+                if (!(sdf > -fp.tau) || !inrange) return;
+                const unsigned long long lk = pack_leaf(kx >> 3, ky >> 3, kz >> 3);
+                if (lk != cur) {
+                    cur = lk;
+                    if (sub == 0 && nrun < kMaxRuns) s_key[ray][nrun] = lk;
+                    nrun++;
+                }
+                if (sub == 0 && ncell < kBackCells)
+                    s_cell[ray][ncell] = ((nrun - 1) << 9) | ((kx & 7) << 6) | ((ky & 7) << 3) | (kz & 7);
+                if (sdf < fp.tau) inner |= 1ull << ncell;
+                ncell++;
+            });
+            // (a ray within the limits has at most kMaxRuns leaf runs and fewer cells)
+            valid = started && inrange && nrun <= kMaxRuns && ncell <= kBackCells;
+        }
     }
+    if (!valid) ncell = nrun = 0;
+    wave_sync();
+    for (int q = sub; q < nrun; q += 4) s_slot[ray][q] = map_find(md, s_key[ray][q]);
+    wave_sync();
+    for (int j = sub; j < ncell; j += 4) {
+        const int c = s_cell[ray][j], off = c & 511, slot = s_slot[ray][c >> 9];
+        // (a leaf or page that is not there: the inputs differ from the integrated ones)
+        const int page = slot >= 0 ? md.leaf_page[(size_t)slot * kLeafPages + (off >> 6)] : -1;
+        s_cell[ray][j] = page >= 0 ? page * kPageVoxels + (off & (kPageVoxels - 1)) : -1;
+    }
+    wave_sync();
+    const int nv = lp.adj_stride / 4;
+    float G[NVL][4];
+#pragma unroll
+    for (int v = 0; v < NVL; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) G[v][e] = 0.0f;
+    float gr = 0.0f;
+    constexpr int U = 4;
+    for (int j0 = 0; j0 < ncell; j0 += U) {
+        float4 a[U][NVL];
+        int rec[U], cnt[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            rec[u] = j0 + u < ncell ? s_cell[ray][j0 + u] : -1;
+            const size_t r = (size_t)(rec[u] >= 0 ? rec[u] : 0);
+            cnt[u] = lp.adj_cnt[r];
+#pragma unroll
+            for (int v = 0; v < NVL; ++v) {
+                const int q = sub + 4 * v;
+                a[u][v] = ((const float4 *)(lp.adj + r * lp.adj_stride))[q < nv ? q : 0];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // a voxel without a row (unlisted, or an unobserved record of an
+            // observed slab) has zero adjoints
+            if (rec[u] < 0 || !(cnt[u] & kAdjRow)) continue;
+#pragma unroll
+            for (int v = 0; v < NVL; ++v) {
+                const float x[4] = {a[u][v].x, a[u][v].y, a[u][v].z, a[u][v].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int k = 4 * (sub + 4 * v) + e;
+                    if (k < K) G[v][e] += x[e];
+                    if (k == K && ((inner >> (j0 + u)) & 1ull) && x[e] != 0.0f)
+                        gr += x[e] / md.vox[(size_t)rec[u] * md.rec_stride + 1];
+                }
+            }
+        }
+    }
+    if (i >= fp.n) return;
     const float sc = grad_scale ? grad_scale[0] : 1.0f;
-    float l[KMAX];
+    const float *row = (const float *)fp.sem + (size_t)i * K;
+    float *out = grad_logits + (size_t)i * K;
+    const bool vec = (K & 3) == 0 && (((uintptr_t)fp.sem | (uintptr_t)grad_logits) & 15u) == 0;
+    float l[NVL][4];
     float mx = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        l[k] = k < K ? ((const float *)fp.sem)[(size_t)i * K + k] : -INFINITY;
-        mx = fmaxf(mx, l[k]);
+    for (int v = 0; v < NVL; ++v) {
+        const int k0 = 4 * (sub + 4 * v);
+        if (vec) {
+            const float4 q = k0 < K ? *(const float4 *)(row + k0) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            l[v][0] = q.x;
+            l[v][1] = q.y;
+            l[v][2] = q.z;
+            l[v][3] = q.w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) l[v][e] = k0 + e < K ? row[k0 + e] : -INFINITY;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mx = fmaxf(mx, l[v][e]);
     }
+    // sums over the ray's four lanes
+    auto quad = [](float x) {
+        x += __shfl_xor(x, 1, 64);
+        return x + __shfl_xor(x, 2, 64);
+    };
+    mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
     float den = 0.0f;
 #pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        l[k] = k < K ? expf(l[k] - mx) : 0.0f;
-        den += l[k];
-    }
+    for (int v = 0; v < NVL; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            l[v][e] = 4 * (sub + 4 * v) + e < K ? expf(l[v][e] - mx) : 0.0f;
+            den += l[v][e];
+        }
+    den = quad(den);
     float pg = 0.0f;
 #pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        l[k] /= den;
-        pg += l[k] * G[k];
-    }
+    for (int v = 0; v < NVL; ++v)
 #pragma unroll
-    for (int k = 0; k < KMAX; ++k)
-        if (k < K) grad_logits[(size_t)i * K + k] = valid ? sc * l[k] * (G[k] - pg) : 0.0f;
-    grad_ranges[i] = valid ? sc * gr : 0.0f;
+        for (int e = 0; e < 4; ++e) {
+            l[v][e] /= den;
+            pg += l[v][e] * G[v][e];
+        }
+    pg = quad(pg);
+#pragma unroll
+    for (int v = 0; v < NVL; ++v) {
+        const int k0 = 4 * (sub + 4 * v);
+        float x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = valid ? sc * l[v][e] * (G[v][e] - pg) : 0.0f;
+        if (vec) {
+            if (k0 < K) *(float4 *)(out + k0) = make_float4(x[0], x[1], x[2], x[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (k0 + e < K) out[k0 + e] = x[e];
+        }
+    }
+    gr = quad(gr);  // (only the lane that holds dL/dD has a term)
+    if (sub == 0) grad_ranges[i] = valid ? sc * gr : 0.0f;
 }
 
 hipError_t launch_backward(const FrameParams &fp, const MapDev &md, const LossParams &lp, const float *grad_scale,
                            float *grad_logits, float *grad_ranges, hipStream_t s)
 {
-    const int b = (fp.n + 255) / 256;
+    const int b = (fp.n + kBackRays - 1) / kBackRays;
     if (b == 0) return hipGetLastError();
-    if (fp.K > 16) hipLaunchKernelGGL(k_backward_rays<32>, dim3(b), dim3(256), 0, s, fp, md, lp, grad_scale, grad_logits, grad_ranges);
-    else if (fp.K > 8) hipLaunchKernelGGL(k_backward_rays<16>, dim3(b), dim3(256), 0, s, fp, md, lp, grad_scale, grad_logits, grad_ranges);
-    else hipLaunchKernelGGL(k_backward_rays<8>, dim3(b), dim3(256), 0, s, fp, md, lp, grad_scale, grad_logits, grad_ranges);
+    const dim3 grid(b), block(4 * kBackRays);
+    // a row holds K + 1 adjoints, 16 to each vector of the four lanes
+    if (fp.K > 31) hipLaunchKernelGGL(k_backward_rays<3>, grid, block, 0, s, fp, md, lp, grad_scale, grad_logits, grad_ranges);
+    else if (fp.K > 15) hipLaunchKernelGGL(k_backward_rays<2>, grid, block, 0, s, fp, md, lp, grad_scale, grad_logits, grad_ranges);
+    else hipLaunchKernelGGL(k_backward_rays<1>, grid, block, 0, s, fp, md, lp, grad_scale, grad_logits, grad_ranges);
     return hipGetLastError();
 }
 
