@@ -3329,7 +3329,7 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_samples(FrameParams fp, M
 // adjoints dL/dc and dL/dD, block partials of the cross-entropy.  Bound by the
 // records read and the rows written, both as 16-byte vectors; the number of
 // samples in the map is summed by the whole workgroup (one thread did it before:
-// 591,000 voxels and 40 blocks of samples 220 -> @LV@ us).
+// 591,000 voxels and 40 blocks of samples 220 -> 51 us).
 __global__ __launch_bounds__(kLossThreads) void k_loss_voxels(FrameParams fp, MapDev md, LossParams lp, int nsb)
 {
     __shared__ float red[kLossThreads];
@@ -3444,7 +3444,7 @@ hipError_t launch_loss(const FrameParams &fp, const MapDev &md, const LossParams
 // then look up the leaves side by side, then the cells' records, and then each
 // adds its 16-byte vectors of the rows, four cells in flight.  (One lane per
 // ray, which waited for the lookup, the page and the row of every cell in turn,
-// took 62 us for 65,536 rays and 20 classes; this takes @BW@ us.)
+// took 62 us for 65,536 rays and 20 classes; this takes 25 us.)
 // NVL: vectors of a row per lane; row vector v belongs to lane v mod 4.
 constexpr int kBackRays = 64;               // rays per workgroup
 constexpr int kBackCells = 3 * 12 + 4 + 1;  // cells of a ray (sdf_trunc <= 6 voxel_size), odd row stride
