@@ -347,8 +347,11 @@ struct RenderParams {
     int maxsteps, width, height;
     int mode, K;           // SLIM_SEM_* and classes, for the label
 };
-hipError_t launch_render(const MapDev &md, const RenderParams &rp, float *depth, int32_t *key, int32_t *label,
-                         hipStream_t s);
+// bits of the render's filters: leaves (32 KB), then blocks of leaves (4 KB)
+constexpr int kFilterLog2 = 18, kFilterBlockLog2 = 15;
+constexpr int kFilterWords = ((1 << kFilterLog2) + (1 << kFilterBlockLog2)) / 32;
+hipError_t launch_render(const MapDev &md, const RenderParams &rp, uint32_t *filter /* kFilterWords, scratch */,
+                         float *depth, int32_t *key, int32_t *label, hipStream_t s);
 hipError_t launch_query(const MapDev &md, int nsem, float vs, const float *xyz, long long m, float *d, float *w,
                         float *sem, hipStream_t s);
 

@@ -4273,15 +4273,87 @@ hipError_t launch_predict(const MapDev &md, const PredictParams &pp, const float
 // render: first surface per pixel (the map-viewing role of Sec. III-E)
 // ---------------------------------------------------------------------------
 
-// One thread per pixel.  The ray is formed as a sensor point at unit depth is
-// (same binary32 operations), walked with the integration walk's stepping rule
-// over [t0, t1], and stops at the first pair of consecutive observed cells with
-// D > 0 then D <= 0; the depth interpolates the cell centres' projections onto
-// the ray linearly in D.  The leaf slot is cached while the walk stays in a leaf.
-__global__ __launch_bounds__(256) void k_render(const MapDev md, const RenderParams rp, float *depth, int32_t *key,
-                                                int32_t *label)
+// Filters of one render: a bit per leaf, and per block of 8 x 8 x 8 leaves, taken
+// at their coordinates modulo 64 leaves and 32 blocks, set for every leaf of the
+// map, so that a clear bit means that nothing is there.  A ray through empty space
+// then reads LDS instead of the leaf table.  (x, y, z: voxel keys.)
+__device__ __forceinline__ uint32_t leaf_bit(int x, int y, int z)
 {
-    const int px = blockIdx.x * 64 + (threadIdx.x & 63), py = blockIdx.y * 4 + (threadIdx.x >> 6);
+    return (((uint32_t)x >> 3) & 63u) | ((((uint32_t)y >> 3) & 63u) << 6) | ((((uint32_t)z >> 3) & 63u) << 12);
+}
+
+__device__ __forceinline__ uint32_t block_bit(int x, int y, int z)
+{
+    return (1u << kFilterLog2) +
+           ((((uint32_t)x >> 6) & 31u) | ((((uint32_t)y >> 6) & 31u) << 5) | ((((uint32_t)z >> 6) & 31u) << 10));
+}
+static_assert(kFilterLog2 == 18 && kFilterBlockLog2 == 15, "6 bits of each leaf coordinate, 5 of each block's");
+
+__global__ __launch_bounds__(256) void k_render_filter_clear(uint32_t *filter)
+{
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kFilterWords / 4) ((uint4 *)filter)[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+__global__ __launch_bounds__(256) void k_render_filter(const MapDev md, uint32_t *filter)
+{
+    const unsigned long long n = md.st->leaves_used;
+    for (unsigned long long i = blockIdx.x * (unsigned long long)blockDim.x + threadIdx.x; i < n;
+         i += (unsigned long long)gridDim.x * blockDim.x) {
+        const unsigned long long k = md.leaf_key[i];
+        const int x = ((int)((k >> 36) & 0x3FFFF) - kLeafBias) * 8, y = ((int)((k >> 18) & 0x3FFFF) - kLeafBias) * 8;
+        const int z = ((int)(k & 0x3FFFF) - kLeafBias) * 8;
+        const uint32_t b = leaf_bit(x, y, z), c = block_bit(x, y, z);
+        atomicOr(&filter[b >> 5], 1u << (b & 31));
+        atomicOr(&filter[c >> 5], 1u << (c & 31));
+    }
+}
+
+// One step of a render's walk (ties step the lowest axis): tm advances by td along
+// the axis of the next crossing, the cell's place by that axis' step.
+__device__ __forceinline__ void render_step(float &tx, float &ty, float &tz, uint32_t &at, float &tnext, bool &ix,
+                                            float tdx, float tdy, float tdz, uint32_t stx, uint32_t sty, uint32_t stz)
+{
+    const bool xy = tx <= ty;
+    const float txy = xy ? tx : ty;
+    const uint32_t sxy = xy ? stx : sty;
+    const bool iz = !(txy <= tz), iy = !xy && !iz;
+    ix = xy && !iz;
+    tnext = iz ? tz : txy;
+    at += iz ? stz : sxy;
+    tx = ix ? tx + tdx : tx;
+    ty = iy ? ty + tdy : ty;
+    tz = iz ? tz + tdz : tz;
+}
+
+// One thread per pixel, a wave per 8 x 8 pixels (neighbouring rays cross the same
+// leaves).  The ray is formed as a sensor point at unit depth is (same binary32
+// operations), walked with the integration walk's stepping rule over [t0, t1], and
+// stops at the first pair of consecutive observed cells with D > 0 then D <= 0; the
+// depth interpolates the cell centres' projections onto the ray linearly in D.
+// Bound by the instructions of a step, of which a ray takes up to a thousand, most
+// of them in empty space.  The cell's place in its block of 64 cells a side is one
+// word of three 8-bit fields (place + 64), and a step through an empty block or leaf
+// is the choice of the axis, three conditional additions, one to the fields and one
+// test of their upper bits; lookups and the test for the ray's end wait for the way
+// out.  In a leaf of the map 8 cells are stepped through before their occupancy, then
+// their D, are read side by side.  1209 x 448 pixels over 8,200 leaves 675 -> 420 us
+// (474 with one cell's reads at a time; 468 with 4 cells and 8 waves per SIMD).  (Jumping to the way out of
+// an empty block in closed form, exact while tm stays in a binade, took 1,143 us: too
+// many rays are at a binade's end somewhere in the wave.)
+constexpr int kRenderThreads = 256, kRenderCells = 8;
+
+__global__ __launch_bounds__(kRenderThreads) void k_render(const MapDev md, const RenderParams rp,
+                                                           const uint32_t *filter, float *depth, int32_t *key,
+                                                           int32_t *label)
+{
+    __shared__ uint32_t s_filter[kFilterWords];
+    for (int i = threadIdx.x; i < kFilterWords / 4; i += kRenderThreads)
+        ((uint4 *)s_filter)[i] = ((const uint4 *)filter)[i];
+    __syncthreads();
+    // 4 waves of 8 x 8 pixels
+    const int lane = lane_id(), wv = threadIdx.x >> 6;
+    const int px = blockIdx.x * 32 + wv * 8 + (lane & 7), py = blockIdx.y * 8 + (lane >> 3);
     if (px >= rp.width || py >= rp.height) return;
     const long long i = (long long)py * rp.width + px;
     float out_d = NAN;
@@ -4298,86 +4370,151 @@ __global__ __launch_bounds__(256) void k_render(const MapDev md, const RenderPar
         u[1] = d1 / r;
         u[2] = d2 / r;
         const float vs = rp.vs, t0 = rp.t0, h = 0.5f * vs;
-        int c[3], stp[3];
+        int k[3], stp[3];
         float tm[3], td[3];
-        bool start_ok = true;
+        bool go = true;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const float s = fmaf(t0, u[a], rp.t[a]);
             const float fc = floorf(s / vs);
-            start_ok = start_ok && fabsf(fc) < kCellLimit;
-            c[a] = fabsf(fc) < kCellLimit ? (int)fc : 0;
+            go = go && fabsf(fc) < kCellLimit;
+            const int c = fabsf(fc) < kCellLimit ? (int)fc : 0;
             if (u[a] > 0.0f) {
                 stp[a] = 1;
-                tm[a] = t0 + fmaf((float)(c[a] + 1), vs, -s) / u[a];
+                tm[a] = t0 + fmaf((float)(c + 1), vs, -s) / u[a];
                 td[a] = vs / u[a];
             } else if (u[a] < 0.0f) {
                 stp[a] = -1;
-                tm[a] = t0 + fmaf((float)c[a], vs, -s) / u[a];
+                tm[a] = t0 + fmaf((float)c, vs, -s) / u[a];
                 td[a] = -vs / u[a];
             } else {
                 stp[a] = 0;
                 tm[a] = INFINITY;
                 td[a] = INFINITY;
             }
+            k[a] = rp.a[a] + c;
+            go = go && key_ok(k[a]);
         }
-        unsigned long long cur = kEmptyKey;
-        int slot = -1;
         bool have_prev = false;
         float Dp = 0.0f, sp = 0.0f;
-        for (int it = 0; it < (start_ok ? rp.maxsteps : 0); ++it) {
-            const int kx = rp.a[0] + c[0], ky = rp.a[1] + c[1], kz = rp.a[2] + c[2];
-            if (!(key_ok(kx) && key_ok(ky) && key_ok(kz))) break;
-            const unsigned long long lk = pack_leaf(kx >> 3, ky >> 3, kz >> 3);
-            if (lk != cur) {
-                cur = lk;
-                slot = map_find(md, lk);
+        const uint32_t stx = (uint32_t)stp[0] << 16, sty = (uint32_t)stp[1] << 8, stz = (uint32_t)stp[2];
+        const float tdx = td[0], tdy = td[1], tdz = td[2];
+        float tx = tm[0], ty = tm[1], tz = tm[2];
+        uint32_t at = 0;
+        constexpr uint32_t kBias = (64u << 16) | (64u << 8) | 64u;
+        constexpr uint32_t kBlockBits = (0xC0u << 16) | (0xC0u << 8) | 0xC0u;  // change on the way out of a block
+        constexpr uint32_t kLeafBits = (0xF8u << 16) | (0xF8u << 8) | 0xF8u;   // or of a leaf
+        int it = 0;
+        // one round per empty block or leaf, or leaf of the map
+        while (go && it < rp.maxsteps) {
+            // (past the key range no cell is observed, and a ray does not come back)
+            if (((uint32_t)(k[0] + kKeyLimit) | (uint32_t)(k[1] + kKeyLimit) | (uint32_t)(k[2] + kKeyLimit)) >= 2u * kKeyLimit)
+                break;
+            const uint32_t bb = block_bit(k[0], k[1], k[2]), lb = leaf_bit(k[0], k[1], k[2]);
+            const uint32_t bw = s_filter[bb >> 5], lw = s_filter[lb >> 5];
+            uint32_t bits = kBlockBits;
+            int slot = -1;
+            if ((bw >> (bb & 31)) & 1u) {
+                bits = kLeafBits;
+                if ((lw >> (lb & 31)) & 1u) slot = map_find(md, pack_leaf(k[0] >> 3, k[1] >> 3, k[2] >> 3));
             }
-            long long rec = -1;
-            if (slot >= 0) {
-                const int off = ((kx & 7) << 6) | ((ky & 7) << 3) | (kz & 7);
-                if ((md.leaf_occ[(size_t)slot * kMaskWords + (off >> 5)] >> (off & 31)) & 1u)
-                    rec = (long long)md.leaf_page[(size_t)slot * kLeafPages + (off >> 6)] * kPageVoxels +
-                          (off & (kPageVoxels - 1));
-            }
-            if (rec < 0) {
+            const int l[3] = {k[0] >> 3, k[1] >> 3, k[2] >> 3};
+            at = kBias + (((uint32_t)k[0] & 63u) << 16) + (((uint32_t)k[1] & 63u) << 8) + ((uint32_t)k[2] & 63u);
+            const uint32_t at0 = at, home = at & bits;
+            if (slot < 0) {
                 have_prev = false;
+                float tnext = 0.0f;
+                bool ix;
+                int n = 0;
+                // (a way out takes at most 3 x 63 + 1 steps)
+                do {
+                    render_step(tx, ty, tz, at, tnext, ix, tdx, tdy, tdz, stx, sty, stz);
+                    ++n;
+                } while ((at & bits) == home && n < 192);
+                it += n;
+                // crossings come in order: one past the end on the way makes the last one so
+                if (tnext > rp.t1) break;
             } else {
-                const float *R = md.vox + (size_t)rec * md.rec_stride;
-                const float D = R[0];
-                const float qx = fmaf((float)c[0], vs, h) - rp.t[0];
-                const float qy = fmaf((float)c[1], vs, h) - rp.t[1];
-                const float qz = fmaf((float)c[2], vs, h) - rp.t[2];
-                const float sk = fmaf(qz, u[2], fmaf(qy, u[1], qx * u[0]));
-                if (have_prev && Dp > 0.0f && D <= 0.0f) {
-                    out_d = sp + (sk - sp) * (Dp / (Dp - D));
-                    ok[0] = kx;
-                    ok[1] = ky;
-                    ok[2] = kz;
-                    if (rp.mode == SLIM_SEM_CLOSED) {
-                        float best = R[2];
-                        out_l = 0;
-                        for (int k = 1; k < rp.K; ++k)
-                            if (R[2 + k] > best) {
-                                best = R[2 + k];
-                                out_l = k;
-                            }
-                    } else if (rp.mode == SLIM_SEM_CLOSED_LAST) {
-                        out_l = (int)R[2];
+                // kRenderCells cells at a time: stepped through first, then their occupancy
+                // and pages read side by side, then their D, then looked at in order
+                bool inside = true;
+                while (inside && it < rp.maxsteps) {
+                    uint32_t cell[kRenderCells], word[kRenderCells];
+                    int page[kRenderCells];
+                    float D[kRenderCells];
+                    int n = 0;
+#pragma unroll
+                    for (int c = 0; c < kRenderCells; ++c) {
+                        cell[c] = at;
+                        if (inside) {
+                            float tnext;
+                            bool ix;
+                            render_step(tx, ty, tz, at, tnext, ix, tdx, tdy, tdz, stx, sty, stz);
+                            ++n;
+                            go = !(tnext > rp.t1);
+                            inside = go && (at & kLeafBits) == home;
+                        }
                     }
-                    break;
+#pragma unroll
+                    for (int c = 0; c < kRenderCells; ++c) {
+                        const uint32_t x = (cell[c] >> 16) & 7u;
+                        word[c] = c < n ? md.leaf_occ[(size_t)slot * kMaskWords + 2 * x + ((cell[c] >> 10) & 1u)] : 0u;
+                        page[c] = c < n ? md.leaf_page[(size_t)slot * kLeafPages + x] : 0;
+                    }
+#pragma unroll
+                    for (int c = 0; c < kRenderCells; ++c) {
+                        const bool on = (word[c] >> (((cell[c] >> 5) & 24u) | (cell[c] & 7u))) & 1u;
+                        const uint32_t off = ((cell[c] >> 5) & 56u) | (cell[c] & 7u);
+                        D[c] = on ? md.vox[((size_t)page[c] * kPageVoxels + off) * md.rec_stride] : NAN;
+                        word[c] = on ? 1u : 0u;
+                    }
+                    int hit = -1;
+#pragma unroll
+                    for (int c = 0; c < kRenderCells; ++c) {
+                        if (c >= n || hit >= 0) continue;
+                        if (!word[c]) {
+                            have_prev = false;
+                            continue;
+                        }
+                        const int kx = l[0] * 8 + (int)((cell[c] >> 16) & 7u), ky = l[1] * 8 + (int)((cell[c] >> 8) & 7u);
+                        const int kz = l[2] * 8 + (int)(cell[c] & 7u);
+                        const float qx = fmaf((float)(kx - rp.a[0]), vs, h) - rp.t[0];
+                        const float qy = fmaf((float)(ky - rp.a[1]), vs, h) - rp.t[1];
+                        const float qz = fmaf((float)(kz - rp.a[2]), vs, h) - rp.t[2];
+                        const float sk = fmaf(qz, u[2], fmaf(qy, u[1], qx * u[0]));
+                        if (have_prev && Dp > 0.0f && D[c] <= 0.0f) {
+                            out_d = sp + (sk - sp) * (Dp / (Dp - D[c]));
+                            ok[0] = kx;
+                            ok[1] = ky;
+                            ok[2] = kz;
+                            hit = page[c];
+                        }
+                        have_prev = true;
+                        Dp = D[c];
+                        sp = sk;
+                    }
+                    it += n;
+                    if (hit >= 0) {
+                        const uint32_t off = (uint32_t)(((ok[0] & 7) << 3 | (ok[1] & 7)) << 3 | (ok[2] & 7)) & (kPageVoxels - 1);
+                        const float *R = md.vox + ((size_t)hit * kPageVoxels + off) * md.rec_stride;
+                        if (rp.mode == SLIM_SEM_CLOSED) {
+                            float best = R[2];
+                            out_l = 0;
+                            for (int c = 1; c < rp.K; ++c)
+                                if (R[2 + c] > best) {
+                                    best = R[2 + c];
+                                    out_l = c;
+                                }
+                        } else if (rp.mode == SLIM_SEM_CLOSED_LAST) {
+                            out_l = (int)R[2];
+                        }
+                        go = inside = false;
+                    }
                 }
-                have_prev = true;
-                Dp = D;
-                sp = sk;
             }
-            const bool xy = tm[0] <= tm[1];
-            const int ax = xy ? (tm[0] <= tm[2] ? 0 : 2) : (tm[1] <= tm[2] ? 1 : 2);
-            const float tnext = ax == 0 ? tm[0] : (ax == 1 ? tm[1] : tm[2]);
-            if (tnext > rp.t1) break;
-            if (ax == 0) { c[0] += stp[0]; tm[0] += td[0]; }
-            else if (ax == 1) { c[1] += stp[1]; tm[1] += td[1]; }
-            else { c[2] += stp[2]; tm[2] += td[2]; }
+            k[0] += (int)((at >> 16) & 255u) - (int)((at0 >> 16) & 255u);
+            k[1] += (int)((at >> 8) & 255u) - (int)((at0 >> 8) & 255u);
+            k[2] += (int)(at & 255u) - (int)(at0 & 255u);
         }
     }
     depth[i] = out_d;
@@ -4389,12 +4526,14 @@ __global__ __launch_bounds__(256) void k_render(const MapDev md, const RenderPar
     if (label) label[i] = out_l;
 }
 
-hipError_t launch_render(const MapDev &md, const RenderParams &rp, float *depth, int32_t *key, int32_t *label,
-                         hipStream_t s)
+hipError_t launch_render(const MapDev &md, const RenderParams &rp, uint32_t *filter, float *depth, int32_t *key,
+                         int32_t *label, hipStream_t s)
 {
     if (rp.width <= 0 || rp.height <= 0) return hipGetLastError();
-    const dim3 grid((rp.width + 63) / 64, (rp.height + 3) / 4);
-    hipLaunchKernelGGL(k_render, grid, dim3(256), 0, s, md, rp, depth, key, label);
+    hipLaunchKernelGGL(k_render_filter_clear, dim3((kFilterWords / 4 + 255) / 256), dim3(256), 0, s, filter);
+    hipLaunchKernelGGL(k_render_filter, dim3(256), dim3(256), 0, s, md, filter);
+    const dim3 grid((rp.width + 31) / 32, (rp.height + 7) / 8);
+    hipLaunchKernelGGL(k_render, grid, dim3(kRenderThreads), 0, s, md, rp, filter, depth, key, label);
     return hipGetLastError();
 }
 

@@ -64,3 +64,30 @@ def test_render_empty_map_and_bad_args():
     assert torch.isnan(out["depth"]).all() and (out["label"] == -1).all()
     with pytest.raises(sv.SlimError):
         g.render(np.eye(4), (10.0, 10.0, 8.0, 6.0), 16, 12, 5.0, 1.0)
+
+
+@pytest.mark.parametrize("W,H,shift", [(1, 1, (0.0, 0.0, 0.0)), (7, 9, (-40.0, 30.0, -7.0)), (33, 17, (0.0, -2.0, -1.5)),
+                                       (64, 16, (20000.0, -20000.0, 0.4)), (65, 31, (-3.0, -2.5, 9000.0))])
+def test_render_partial_tiles_and_far_maps(W, H, shift):
+    """Images that fill their 32 x 16 tiles in part, with an axis-aligned ray among them, over maps on either side of
+    the origin and far from it: the oracle's hits, voxels and labels where its decisions are clear."""
+    vs, tau, K = 0.05, 0.15, 5
+    g, o = make_pair(vs, tau, 0.0, 100.0, sv.SEM_CLOSED, K)
+    off = np.asarray(shift)
+    for fr in synth.room_sequence(3, seed=6, yaw_span=1.0, width=64, height=48, f=53.3, cx=32.0, cy=24.0):
+        pose = fr["pose"].copy()
+        pose[:3, 3] += off
+        integrate_both(g, o, fr["points"], pose, fr["label"], sv.IN_LABEL_I32)
+    pose = synth.pose_matrix(synth.camera_rotation((1.0, 0.0, 0.0)), np.array([2.0312, 1.9687, 1.4219]) + off)
+    intr = (0.6 * max(W, 8), 0.6 * max(W, 8), float(W // 2), float(H // 2))
+    gout = g.render(pose, intr, W, H, 0.05, 6.0)
+    oout = oracle.render(o, pose, *intr, W, H, 0.05, 6.0)
+    gd, gk, gl = (gout[k].cpu().numpy() for k in ("depth", "key", "label"))
+    od, clear = oout["depth"], oout["margin"] > 1e-2 * tau
+    ohit = np.isfinite(od)
+    assert np.array_equal(np.isfinite(gd)[clear], ohit[clear])
+    both = clear & ohit
+    assert np.array_equal(gk[both], oout["key"][both]) and np.array_equal(gl[both], oout["label"][both])
+    assert np.all(np.abs(gd[both] - od[both]) <= 2e-6 * od[both] + 1e-5 * tau * np.sqrt(3.0) * vs / oout["margin"][both]
+                  + 1e-6)
+    assert both.sum() >= (1 if W == 1 else W * H // 4)
