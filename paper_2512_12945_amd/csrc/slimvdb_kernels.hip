@@ -1346,25 +1346,31 @@ __device__ __forceinline__ void combine_wave_vec(const FrameParams &fp, const Ma
                         lane < n ? vals[lane] : 0.0f);
 }
 
+// Components per lane of the general wave combine (a row of up to 64 J
+// components), and observations whose rows are in flight at once.
 constexpr int kWaveComps = 16;
-constexpr int kWaveBatch = 4;  // observations whose rows are in flight at once
+constexpr int wave_batch(int j) { return j <= 2 ? 8 : 4; }
 
 // One voxel, one wave: lane l owns components l, l + 64, ... of the open-set
-// statistics (L <= 1024) or of the class counts (K <= 1024).  The rows of
-// kWaveBatch observations are loaded before any is used.  Open set: one pass
+// statistics (L <= 64 J) or of the class counts (K <= 64 J).  The rows of
+// kWaveBatch observations are loaded before any is used; up to two components per
+// lane the record is requested before the rows.  Open set: one pass
 // over the observations with sums shifted by the first one, s1 = sum (z - z_0),
 // s2 = sum (z - z_0)^2, so the batch mean is z_0 + s1 / n and the scatter
 // s2 - s1^2 / n (the shift keeps the subtraction well conditioned).
+template <int J>
 __device__ __forceinline__ void combine_wave(const FrameParams &fp, const MapDev &md, const uint32_t *keys,
                                              const float *vals, uint32_t n, long long rec, bool existed)
 {
+    constexpr int kWaveBatch = wave_batch(J);
+    constexpr bool early = J <= 2;
     const int lane = lane_id();
     const bool open = fp.L > 0;
     const int C = open ? fp.L : fp.K;
     float *R = md.vox + (size_t)rec * md.rec_stride;
-    float s1[kWaveComps], s2[kWaveComps];
+    float s1[J], s2[J];
 #pragma unroll
-    for (int j = 0; j < kWaveComps; ++j) {
+    for (int j = 0; j < J; ++j) {
         s1[j] = 0.0f;
         s2[j] = 0.0f;
     }
@@ -1372,31 +1378,42 @@ __device__ __forceinline__ void combine_wave(const FrameParams &fp, const MapDev
     // indices come from the lanes, so its rows do not wait on a load of them
     // (batches start at multiples of their size and never cross a window)
     uint32_t kl = (uint32_t)lane < n ? keys[lane] & kPidMask : 0u;
+    const float vl = (uint32_t)lane < n ? vals[lane] : 0.0f;
+    const float W0 = existed ? R[1] : 0.0f, D0 = existed ? R[0] : 0.0f;
+    float m0[early ? J : 1], b0[early ? J : 1];
+    if constexpr (early) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int comp = lane + 64 * j;
+            m0[j] = existed && comp < C ? R[2 + comp] : 0.0f;
+            b0[j] = open && existed && comp < C ? R[2 + C + comp] : 0.0f;
+        }
+    }
     auto window = [&](uint32_t q) {
         if (q > 0 && (q & 63u) == 0) kl = q + (uint32_t)lane < n ? keys[q + lane] & kPidMask : 0u;
     };
     auto pid_at = [&](uint32_t t) { return (uint32_t)__shfl((int)kl, (int)(t & 63u), 64); };
     if (open) {
-        float z0[kWaveComps];
+        float z0[J];
         const uint32_t p0 = pid_at(0);
 #pragma unroll
-        for (int j = 0; j < kWaveComps; ++j) z0[j] = (lane + 64 * j < C) ? load_emb(fp, p0, lane + 64 * j) : 0.0f;
+        for (int j = 0; j < J; ++j) z0[j] = (lane + 64 * j < C) ? load_emb(fp, p0, lane + 64 * j) : 0.0f;
         // observation 0 enters as its own difference, 0
         for (uint32_t q = 0; q < n; q += kWaveBatch) {
             window(q);
-            float z[kWaveBatch][kWaveComps];
+            float z[kWaveBatch][J];
 #pragma unroll
             for (int b = 0; b < kWaveBatch; ++b) {
                 const bool has = q + b < n && q + b > 0;
                 const uint32_t pid = pid_at(q + b);
 #pragma unroll
-                for (int j = 0; j < kWaveComps; ++j)
+                for (int j = 0; j < J; ++j)
                     z[b][j] = (has && lane + 64 * j < C) ? load_emb(fp, pid, lane + 64 * j) : z0[j];
             }
 #pragma unroll
             for (int b = 0; b < kWaveBatch; ++b)
 #pragma unroll
-                for (int j = 0; j < kWaveComps; ++j) {
+                for (int j = 0; j < J; ++j) {
                     const float d = z[b][j] - z0[j];
                     s1[j] += d;
                     s2[j] += d * d;
@@ -1404,20 +1421,27 @@ __device__ __forceinline__ void combine_wave(const FrameParams &fp, const MapDev
         }
         // Eqs. (11)-(14) with lambda = W, nu = W / 2
         const float nf = (float)n;
-        const float W0 = existed ? R[1] : 0.0f, W1 = W0 + nf;
+        const float W1 = W0 + nf;
         const float inv_n = 1.0f / nf, inv_w1 = 1.0f / W1;
         const float cross = W0 * nf * inv_w1;
         float *M = R + 2, *B = R + 2 + fp.L;
 #pragma unroll
-        for (int j = 0; j < kWaveComps; ++j) {
+        for (int j = 0; j < J; ++j) {
             const int comp = lane + 64 * j;
             if (comp < C) {
                 const float zbar = z0[j] + s1[j] * inv_n;
                 const float scat = fmaxf(s2[j] - s1[j] * s1[j] * inv_n, 0.0f);
-                const float m0 = existed ? M[comp] : 0.0f, b0 = existed ? B[comp] : 0.0f;
-                const float dm = zbar - m0;
-                B[comp] = b0 + 0.5f * scat + cross * dm * dm * 0.5f;
-                M[comp] = (W0 * m0 + nf * zbar) * inv_w1;
+                float mi, bi;
+                if constexpr (early) {
+                    mi = m0[j];
+                    bi = b0[j];
+                } else {
+                    mi = existed ? M[comp] : 0.0f;
+                    bi = existed ? B[comp] : 0.0f;
+                }
+                const float dm = zbar - mi;
+                B[comp] = bi + 0.5f * scat + cross * dm * dm * 0.5f;
+                M[comp] = (W0 * mi + nf * zbar) * inv_w1;
             }
         }
     } else if (fp.sem_kind == SLIM_IN_LABEL_I32) {
@@ -1432,25 +1456,25 @@ __device__ __forceinline__ void combine_wave(const FrameParams &fp, const MapDev
 #pragma unroll
             for (int b = 0; b < 2 * kWaveBatch; ++b)
 #pragma unroll
-                for (int j = 0; j < kWaveComps; ++j) s1[j] += (lab[b] == lane + 64 * j) ? 1.0f : 0.0f;
+                for (int j = 0; j < J; ++j) s1[j] += (lab[b] == lane + 64 * j) ? 1.0f : 0.0f;
         }
     } else if (fp.sem_kind == SLIM_IN_PROB_F32) {
         for (uint32_t q = 0; q < n; q += kWaveBatch) {
             window(q);
-            float x[kWaveBatch][kWaveComps];
+            float x[kWaveBatch][J];
 #pragma unroll
             for (int b = 0; b < kWaveBatch; ++b) {
                 const bool has = q + b < n;
                 const uint32_t pid = pid_at(q + b);
                 const size_t row = has ? (size_t)pid * C : 0;
 #pragma unroll
-                for (int j = 0; j < kWaveComps; ++j)
+                for (int j = 0; j < J; ++j)
                     x[b][j] = (has && lane + 64 * j < C) ? ((const float *)fp.sem)[row + lane + 64 * j] : 0.0f;
             }
 #pragma unroll
             for (int b = 0; b < kWaveBatch; ++b)
 #pragma unroll
-                for (int j = 0; j < kWaveComps; ++j) s1[j] += x[b][j];
+                for (int j = 0; j < J; ++j) s1[j] += x[b][j];
         }
     } else {
         // logits, K <= 64: softmax across the wave
@@ -1472,19 +1496,23 @@ __device__ __forceinline__ void combine_wave(const FrameParams &fp, const MapDev
         }
     }
     const float nf = (float)n;
-    const float W0 = existed ? R[1] : 0.0f, W1 = W0 + nf;
-    const float D0 = existed ? R[0] : 0.0f;
+    const float W1 = W0 + nf;
     if (!open) {
 #pragma unroll
-        for (int j = 0; j < kWaveComps; ++j) {
+        for (int j = 0; j < J; ++j) {
             const int comp = lane + 64 * j;
-            if (comp < C) R[2 + comp] = (existed ? R[2 + comp] : 0.0f) + s1[j];
+            if (comp < C) {
+                float c0;
+                if constexpr (early) c0 = m0[j];
+                else c0 = existed ? R[2 + comp] : 0.0f;
+                R[2 + comp] = c0 + s1[j];
+            }
         }
     }
     // fixed-point distance sum, 64 distances loaded at a time, one per lane
     const FixScale fx = fix_scale(fp);
-    long long sum_t = 0;
-    for (uint32_t w0 = 0; w0 < n; w0 += 64)
+    long long sum_t = (uint32_t)lane < n ? fix_q(vl, fx.s) : 0ll;
+    for (uint32_t w0 = 64; w0 < n; w0 += 64)
         sum_t += w0 + (uint32_t)lane < n ? fix_q(vals[w0 + lane], fx.s) : 0ll;
     for (int d = 32; d > 0; d >>= 1) sum_t += __shfl_xor(sum_t, d, 64);
     if (lane == 0) {
@@ -1609,7 +1637,7 @@ __device__ void combine_range(const FrameParams &fp, const MapDev &md, LeafShare
                 combine_wave_vec<(KMAX > 0 ? KMAX : 1)>(fp, md, keys + (sh.bin0[o] - base), vals + (sh.bin0[o] - base),
                                                         n, rec, existed);
             else
-                combine_wave(fp, md, keys + (sh.bin0[o] - base), vals + (sh.bin0[o] - base), n, rec, existed);
+                combine_wave<kWaveComps>(fp, md, keys + (sh.bin0[o] - base), vals + (sh.bin0[o] - base), n, rec, existed);
         }
     }
 }
@@ -2526,7 +2554,7 @@ __global__ __launch_bounds__(kLeafThreads, 3) void k_leaf_acc_batch(MapBatch mb)
 // over all voxels of the frame at once so that the heavy voxels spread over the
 // whole GPU.  Consecutive descriptors (neighbouring voxels, which share
 // observations) go to workgroups on the same XCD.
-template <int KMAX>
+template <int KMAX, int J = kWaveComps>
 __device__ __forceinline__ void voxel_combine_range(const FrameParams &fp, const MapDev &md, uint32_t blk,
                                                     uint32_t nblk)
 {
@@ -2582,7 +2610,7 @@ __device__ __forceinline__ void voxel_combine_range(const FrameParams &fp, const
             else if constexpr (KMAX < 0)
                 combine_last_wave(fp, md, keys, vals, n, (long long)d.x, existed);
             else
-                combine_wave(fp, md, keys, vals, n, (long long)d.x, existed);
+                combine_wave<J>(fp, md, keys, vals, n, (long long)d.x, existed);
         }
     }
 }
@@ -2640,7 +2668,7 @@ __device__ __forceinline__ void voxel_combine_maps(const MapBatch &mb, uint32_t 
         else if constexpr (KMAX < 0)
             combine_last_wave(fp, md, keys, vals, n, (long long)d.x, existed);
         else
-            combine_wave(fp, md, keys, vals, n, (long long)d.x, existed);
+            combine_wave<kWaveComps>(fp, md, keys, vals, n, (long long)d.x, existed);
     }
 }
 
@@ -2652,10 +2680,14 @@ __host__ __device__ constexpr int combine_min_blocks(int kmax)
     return kmax == 1 ? 7 : (kmax == 2 ? 5 : (kmax == 4 ? 7 : (kmax == 8 ? 3 : 1)));
 }
 
-template <int KMAX>
-__global__ __launch_bounds__(256, combine_min_blocks(KMAX)) void k_voxel_combine(FrameParams fp, MapDev md)
+// and the general one with J components per lane
+__host__ __device__ constexpr int general_min_blocks(int j) { return j == 1 ? 7 : (j == 2 ? 6 : (j == 4 ? 4 : 1)); }
+
+template <int KMAX, int J = kWaveComps>
+__global__ __launch_bounds__(256, KMAX == 0 ? general_min_blocks(J) : combine_min_blocks(KMAX)) void k_voxel_combine(
+    FrameParams fp, MapDev md)
 {
-    voxel_combine_range<KMAX>(fp, md, blockIdx.x, gridDim.x);
+    voxel_combine_range<KMAX, J>(fp, md, blockIdx.x, gridDim.x);
 }
 
 template <int KMAX>
@@ -3061,7 +3093,17 @@ static void launch_voxel_combine(int kind, const FrameParams &fp, const MapDev &
 {
     const dim3 gl(blocks), bl(256);
     switch (voxel_combine_arg(kind)) {
-    case 0: hipLaunchKernelGGL((k_voxel_combine<0>), gl, bl, 0, s, fp, md); break;
+    case 0: {
+        // as many components per lane as the rows need: with 16 for every length,
+        // rows of 100 components (2 per lane) went through 8 times the instructions
+        // in 4 waves per CU; 18,600 voxels with 216,000 such rows 247 -> 43 us
+        const int c = fp.L > 0 ? fp.L : fp.K;
+        if (c <= 64) hipLaunchKernelGGL((k_voxel_combine<0, 1>), gl, bl, 0, s, fp, md);
+        else if (c <= 128) hipLaunchKernelGGL((k_voxel_combine<0, 2>), gl, bl, 0, s, fp, md);
+        else if (c <= 256) hipLaunchKernelGGL((k_voxel_combine<0, 4>), gl, bl, 0, s, fp, md);
+        else hipLaunchKernelGGL((k_voxel_combine<0, 16>), gl, bl, 0, s, fp, md);
+        break;
+    }
     case -1: hipLaunchKernelGGL((k_voxel_combine<-1>), gl, bl, 0, s, fp, md); break;
     case 1: hipLaunchKernelGGL((k_voxel_combine<1>), gl, bl, 0, s, fp, md); break;
     case 2: hipLaunchKernelGGL((k_voxel_combine<2>), gl, bl, 0, s, fp, md); break;
