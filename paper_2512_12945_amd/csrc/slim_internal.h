@@ -64,6 +64,11 @@ struct FrameState {
     unsigned int pad_lists[30];
     alignas(128) unsigned long long n_lists_tail;
     unsigned int pad_tail[30];
+    // voxels updated that existed (low half) and voxels created (high half), each
+    // leaf-kernel workgroup adding to one of the words
+    struct alignas(128) Stat {
+        unsigned long long v;
+    } stat[64];
     Line n_vox;       // voxel descriptors for the wave combine
     Line frame_err;   // nonzero: do not apply this frame
 };
@@ -208,8 +213,6 @@ struct MapDev {
     int2 *work;           // work items (index in items_big, slab or range) of large leaves
     uint32_t work_cap;
     uint4 *vox_list;      // wave-combine voxels: (record, pairs | existed << 31, first sorted pair, 0)
-    uint2 *blk_stats;     // per leaf-kernel block: (voxels updated that existed, voxels created)
-    int leaf_blocks;      // grid of the leaf kernel of the current frame (<= kMaxLeafBlocksPerCu * CUs)
     // leaf tiles of the current frame: leaves with at most wave_pairs pairs are
     // one wave's work, sorted leaves with more than slab_pairs pairs are split
     // into x-slab items (0: the largest the kernels hold)
@@ -242,7 +245,7 @@ struct MapBatch {
 struct LaunchShape {
     int plan_blocks;    // leaf planning
     int bucket_blocks;  // pair bucketing
-    int leaf_blocks;    // per-leaf sort and combine (also the size of blk_stats in use)
+    int leaf_blocks;    // per-leaf sort and combine
     int persistent;     // batched calls: 1 one persistent launch, 0 one launch per stage
     int walk_chunk;     // persistent: walk blocks (256 rays each) per ray-chunk item
     int wave_pairs;     // leaf tiles (MapDev::wave_pairs, slab_pairs)

@@ -317,7 +317,6 @@ slim_status slim_map_create(const slim_map_config *config, slim_map **out)
     md.max_leaves = config->max_leaves;
     md.max_pages = (config->max_voxels + kPageVoxels - 1) / kPageVoxels;
     md.rec_stride = record_stride(m->nsem);
-    md.leaf_blocks = m->cus * 16;
     md.wave_pairs = 0;
     md.slab_pairs = 0;
     const size_t L = (size_t)config->max_leaves, NP = (size_t)md.max_pages;
@@ -329,7 +328,7 @@ slim_status slim_map_create(const slim_map_config *config, slim_map **out)
         (r = dalloc(m, &md.items_small, cap)) || (r = dalloc(m, &md.leaf_key, L)) ||
         (r = dalloc(m, &md.leaf_page, L * kLeafPages)) || (r = dalloc(m, &md.leaf_occ, L * kMaskWords)) ||
         (r = dalloc(m, &md.vox, NP * kPageVoxels * (size_t)md.rec_stride)) ||
-        (r = dalloc(m, &md.blk_stats, (size_t)m->cus * kMaxLeafBlocksPerCu)) || (r = dalloc(m, &md.st, 1)) ||
+        (r = dalloc(m, &md.st, 1)) ||
         (r = dalloc(m, &md.fs, 1)) || (r = dalloc(m, &m->filter, kFilterWords))) {
         free_all(m);
         delete m;
@@ -1060,7 +1059,6 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
         r = ensure_pairs(maps[i], (size_t)std::max<int64_t>(f.n, 1) * (size_t)maps[i]->maxsteps, s);
         if (r) return r;
         mds[i] = maps[i]->md;
-        mds[i].leaf_blocks = m0->shape.leaf_blocks;
         mds[i].wave_pairs = m0->shape.wave_pairs;
         mds[i].slab_pairs = m0->shape.slab_pairs;
         start[i + 1] = start[i] + (int)std::max<int64_t>(1, (f.n + kWalkThreads - 1) / kWalkThreads);
@@ -1104,8 +1102,6 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
             c[3] = share(shape.leaf_blocks, i, leaf_cap);
             c[4] = voxel_combine_arg(kinds[i]) != -2 ? share(shape.leaf_blocks, i, 0xFFFFu) : 0u;
             c[5] = 1;
-            // the commit sums the statistics of this many leaf-tile items
-            mds[i].leaf_blocks = (int)c[3];
         }
         for (int st = 0; st < kPersistStages; ++st)
             for (int i = 0; i < nmaps; ++i) {
@@ -1155,9 +1151,6 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
             plan.leaf_blocks[g] = std::max(shape.leaf_blocks, gs);
             plan.leaf_part[g] = (int)part.size();
             share(gm, gs, plan.leaf_blocks[g], part);
-            // the commit sums the statistics of the map's share of leaf blocks
-            for (int q = 0; q < gs; ++q)
-                mds[gm[q]].leaf_blocks = part[plan.leaf_part[g] + q + 1] - part[plan.leaf_part[g] + q];
             plan.comb_part[g] = (int)part.size();
             plan.comb_blocks[g] = 0;
             if (voxel_combine_arg(plan.group_kind[g]) != -2) {
