@@ -24,6 +24,7 @@ constexpr int kLeafPages = kLeafVoxels / kPageVoxels;
 #endif
 constexpr int kWalkThreads = SLIM_WALK_THREADS;  // rays per walk block
 constexpr int kWalkTable = 8 * kWalkThreads;     // block-local leaf table: at most 8 leaf runs per ray
+constexpr int kMaxRuns = 8;                  // leaves a ray visits: sdf_trunc <= 6 voxel_size keeps it within 7
 constexpr int kLeafThreads = 256;
 constexpr int kLeafBatch = 8;                // loads in flight per thread in the leaf kernel
 constexpr int kLeafLdsPairs = kLeafBatch * kLeafThreads;  // pairs a leaf holds in LDS at once
@@ -200,8 +201,12 @@ struct MapDev {
     float *vox;
     int rec_stride;
     // per-frame pair buffers
-    uint4 *pairs;         // the walk's pairs: (staging position of the pair's leaf, rank of the pair
-                          // inside its leaf's bucket, (offset << 23) | point index, truncated distance bits)
+    // the walk's ray records, planes of ray_cap entries: kept cells with the last
+    // visit's index, steps along x, steps along y; and per leaf visited the staging
+    // position and first rank of the ray's run
+    unsigned long long *ray_bits;
+    uint2 *ray_run;
+    size_t ray_cap;
     uint32_t *pair_key;   // leaf-kernel scratch: sorted keys of bins beyond LDS, wave-combine input
     float *pair_tsdf;     // and their truncated distances
     uint2 *srt_kv;        // pairs grouped by leaf: (key, truncated distance bits)
@@ -309,7 +314,8 @@ hipError_t launch_integrate(const FrameParams &fp, const MapDev &md, const Launc
 hipError_t launch_reset(const MapDev &md, hipStream_t s);
 hipError_t launch_reset_staging(const MapDev &md, hipStream_t s);
 hipError_t launch_walk(const FrameParams &fp, const MapDev &md, hipStream_t s, const PassWalk *pw = nullptr);
-hipError_t launch_after_walk(const FrameParams &fp, const MapDev &md, const LaunchShape &shape, hipStream_t s);
+hipError_t launch_after_walk(const FrameParams &fp, const MapDev &md, const LaunchShape &shape, hipStream_t s,
+                             const PassWalk *pw = nullptr);
 hipError_t launch_loss(const FrameParams &fp, const MapDev &md, const LossParams &lp, hipStream_t s);
 hipError_t launch_backward(const FrameParams &fp, const MapDev &md, const LossParams &lp, const float *grad_scale,
                            float *grad_logits, float *grad_ranges, hipStream_t s);

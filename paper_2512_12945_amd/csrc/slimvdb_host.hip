@@ -211,14 +211,16 @@ slim_status ensure_pairs(slim_map *m, size_t need, hipStream_t s, int buf = 0)
     size_t cap = std::max<size_t>(need, pcap + pcap / 2);
     cap = std::min<size_t>(cap, 0xFFFFFFF0ull);
     MapDev &md = buf ? m->md1 : m->md;
-    void *ptrs[10] = {md.pairs,   md.pair_key, md.pair_tsdf, md.srt_kv,  md.srt_lab,
+    void *ptrs[11] = {md.ray_bits, md.ray_run, md.pair_key, md.pair_tsdf, md.srt_kv,  md.srt_lab,
                       md.tmp_key, md.tmp_tsdf, md.work,      md.vox_list, md.items_big};
     for (void *p : ptrs) {
         if (!p) continue;
         (void)hipFree(p);
         m->allocs.erase(std::remove(m->allocs.begin(), m->allocs.end(), p), m->allocs.end());
     }
-    md.pairs = nullptr;
+    md.ray_bits = nullptr;
+    md.ray_run = nullptr;
+    md.ray_cap = 0;
     md.pair_key = md.tmp_key = nullptr;
     md.pair_tsdf = md.tmp_tsdf = nullptr;
     md.srt_kv = nullptr;
@@ -229,7 +231,9 @@ slim_status ensure_pairs(slim_map *m, size_t need, hipStream_t s, int buf = 0)
     // a large leaf has more than kLeafLdsPairs pairs and at most 8 slab items
     const size_t wcap = cap / (kLeafLdsPairs / kLeafPages) + kLeafPages;
     slim_status r;
-    if ((r = dalloc(m, &md.pairs, cap)) ||
+    // rays of `need` pairs, and a partial workgroup of each frame of a pass
+    const size_t rays = cap / (size_t)m->maxsteps + (size_t)kWalkThreads * (kPassFrames + 1);
+    if ((r = dalloc(m, &md.ray_bits, 3 * rays)) || (r = dalloc(m, &md.ray_run, (size_t)kMaxRuns * rays)) ||
         (r = dalloc(m, &md.pair_key, cap)) || (r = dalloc(m, &md.pair_tsdf, cap)) ||
         (r = dalloc(m, &md.srt_kv, cap)) ||
         (r = dalloc(m, &md.srt_lab, cap)) || (r = dalloc(m, &md.tmp_key, cap)) ||
@@ -242,6 +246,7 @@ slim_status ensure_pairs(slim_map *m, size_t need, hipStream_t s, int buf = 0)
         return r;
     }
     pcap = cap;
+    md.ray_cap = rays;
     md.pair_cap = (uint32_t)cap;
     md.work_cap = (uint32_t)wcap;
     return SLIM_OK;
@@ -486,7 +491,9 @@ slim_status ensure_buffer1(slim_map *m, hipStream_t s)
     md.pos_plan = md.pos_pages = nullptr;
     md.items = md.items_small = nullptr;
     md.fs = nullptr;
-    md.pairs = nullptr;
+    md.ray_bits = nullptr;
+    md.ray_run = nullptr;
+    md.ray_cap = 0;
     md.pair_key = md.tmp_key = nullptr;
     md.pair_tsdf = md.tmp_tsdf = nullptr;
     md.srt_kv = nullptr;
@@ -631,7 +638,7 @@ slim_status integrate_passes(slim_map *m, const std::vector<FrameParams> &fps, h
                 HIP_OK(launch_walk(fp, md, m->wstream, pass ? &pw : nullptr));
                 HIP_OK(hipEventRecord(m->ev_walk[b], m->wstream));
                 HIP_OK(hipStreamWaitEvent(s, m->ev_walk[b], 0));
-                HIP_OK(launch_after_walk(fp, md, m->shape, s));
+                HIP_OK(launch_after_walk(fp, md, m->shape, s, pass ? &pw : nullptr));
                 HIP_OK(hipEventRecord(m->ev_free[b], s));
                 m->used[b] = true;
             }

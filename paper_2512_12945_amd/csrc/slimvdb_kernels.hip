@@ -1,16 +1,16 @@
 // HIP kernels of the semantic TSDF integrator (gfx950, wave64).
 //
 // One frame runs as five kernels on the map's stream:
-//   1. ray_walk_emit  one lane per point: pose application, ray, band, voxel
+//   1. ray_walk       one lane per point: pose application, ray, band, voxel
 //                     walk (Sec. III-A), truncation gate.  The leaves the
 //                     block's rays touch are collected in an LDS table, so each
 //                     (block, leaf) makes one staging insert and one bucket
-//                     reservation; every kept (voxel, point) observation is
-//                     written as a pair.
+//                     reservation; the walk is recorded, some 50 bytes a ray.
 //   2. leaf_plan      one lane per touched leaf: find it in the map (or number
 //                     it as new), number record pages for newly touched 8x8
 //                     slabs, allocate its pair bucket.
-//   3. pair_bucket    one lane per pair: scatter into its leaf's bucket.
+//   3. ray_emit       one lane per point: the recorded walk again, every kept
+//                     (voxel, point) observation written to its leaf's bucket.
 //   4. leaf_acc       geometry and int32 labels (K <= 32): one workgroup per
 //                     touched leaf (or one wave per small leaf) adds every pair
 //                     into its voxel's LDS accumulators with integer atomics --
@@ -315,7 +315,6 @@ __device__ void block_scan512(const uint32_t *in, uint32_t *out, uint32_t *wsum)
 // ---------------------------------------------------------------------------
 
 constexpr int kWaveItemPairs = 256;  // leaves with at most this many pairs are one wave's work
-constexpr int kMaxRuns = 8;  // leaf runs per ray; sdf_trunc <= 6 voxel_size keeps a ray within this
 static_assert(kWalkTable >= kWalkThreads * kMaxRuns, "the walk table must hold every run of a block");
 
 __device__ __forceinline__ uint32_t lds_hash(unsigned long long k)
@@ -357,17 +356,23 @@ struct WalkShared {
     uint32_t t_slab[kWalkTable / 4];  // x-slabs of the leaf this block touches (8 bits per entry)
     uint16_t t_list[kWalkTable];      // occupied entries
     uint16_t t_fresh[kWalkTable];     // entries whose staging insert this block made
-    uint32_t s_n, s_nfresh, s_pair_base, wsum[4];
+    uint32_t s_n, s_nfresh, s_pairs;
 };
 
-// One block of the walk: rays blk * blockDim.x + [0, blockDim.x) of a frame.
-__device__ __forceinline__ void walk_emit_block(const FrameParams &fp, const MapDev &md, int blk, WalkShared &ws)
+// One block of the walk: rays blk * blockDim.x + [0, blockDim.x) of a frame, whose
+// records are rblk * blockDim.x + [0, blockDim.x).  A ray's record is what
+// ray_emit_block needs to write its pairs where they belong once the leaves'
+// buckets are laid out: which cells it kept and how it steps (bits), and for each
+// leaf it visits the staging position and the first of its ranks in the leaf's
+// bucket.
+constexpr int kVisitShift = 56;  // kept cells in the low bits (at most 43), the last visit's index above
+
+__device__ __forceinline__ void walk_block(const FrameParams &fp, const MapDev &md, int blk, int rblk, WalkShared &ws)
 {
     unsigned long long *t_key = ws.t_key;
     uint32_t *t_cnt = ws.t_cnt, *t_pos = ws.t_pos, *t_slab = ws.t_slab;
     uint16_t *t_list = ws.t_list, *t_fresh = ws.t_fresh;
-    uint32_t &s_n = ws.s_n, &s_nfresh = ws.s_nfresh, &s_pair_base = ws.s_pair_base;
-    uint32_t *wsum = ws.wsum;
+    uint32_t &s_n = ws.s_n, &s_nfresh = ws.s_nfresh, &s_pairs = ws.s_pairs;
 
     const int tid = threadIdx.x;
     const int i = blk * blockDim.x + tid;
@@ -391,17 +396,17 @@ __device__ __forceinline__ void walk_emit_block(const FrameParams &fp, const Map
     if (tid == 0) {
         s_n = 0;
         s_nfresh = 0;
+        s_pairs = 0;
     }
     __syncthreads();
 
-    // pass 1: the walk, with few instructions a step (a frame of a few thousand
+    // the walk, with few instructions a step (a frame of a few thousand
     // points is one wave per SIMD, whose time is the length of this loop's chain).
     // The cell is held as binary32 coordinates, which the distance is formed from
     // (exact: an accepted cell is within 2^21 of the anchor), and as its place in
     // its leaf, a word of three 5-bit fields (place + 8: bit 3 of a field clears
-    // when the cell leaves the leaf on that axis).  Recorded for pass 2: the first
-    // cell, which steps went along x and y, and which cells passed the gate.  Of
-    // each leaf the ray visits: its kept cells and their x-slabs (16 bits a visit)
+    // when the cell leaves the leaf on that axis).  Recorded: which steps went along
+    // x and y, and which cells passed the gate.  Of each leaf the ray visits: its kept cells and their x-slabs (16 bits a visit)
     // and the axis on which the ray leaves it.  Coordinates are monotone along the
     // ray, so the first and the last cell decide the key range.  (Per-cell leaf keys,
     // key-range tests and run arrays before: 20.5 -> 16.7 us for 20,011 points,
@@ -471,9 +476,9 @@ __device__ __forceinline__ void walk_emit_block(const FrameParams &fp, const Map
     }
     if (!valid) {
         cnt = 0;
+        kept = 0ull;
         info[0] = info[1] = 0ull;
         visit = 0;
-        nvis = 0;
     }
 
     // the visited leaves' runs of kept cells into the block table: local rank of
@@ -518,14 +523,19 @@ __device__ __forceinline__ void walk_emit_block(const FrameParams &fp, const Map
             key += up ? one : 0ull - one;
         }
     }
+    const size_t r = (size_t)rblk * blockDim.x + tid, rcap = md.ray_cap;
+    md.ray_bits[r] = kept | ((unsigned long long)visit << kVisitShift);
+    if (cnt) {
+        md.ray_bits[rcap + r] = stepx;
+        md.ray_bits[2 * rcap + r] = stepy;
+    }
+    uint32_t wcnt = cnt;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) wcnt += __shfl_xor(wcnt, d, 64);
+    if (lane_id() == 0 && wcnt) atomicAdd(&s_pairs, wcnt);
     const uint32_t rejected_block = __syncthreads_count((i < fp.n) && !valid);
-
-    // the block's pair range is reserved while the leaves are staged
-    uint32_t total;
-    const uint32_t off = block_excl_scan(cnt, wsum, &total);
-    uint32_t pair_base = 0;
     if (tid == 0) {
-        if (total) pair_base = atomicAdd(&md.fs->pairs.v, total);
+        if (s_pairs) atomicAdd(&md.fs->pairs.v, s_pairs);
         if (rejected_block) atomicAdd(&md.fs->rejected.v, rejected_block);
     }
     // one staging lookup, one bucket reservation and one slab update per leaf of the block
@@ -543,48 +553,20 @@ __device__ __forceinline__ void walk_emit_block(const FrameParams &fp, const Map
             atomicOr(&md.fs->frame_err.v, 1u);
         }
     }
-    if (tid == 0) s_pair_base = pair_base;
     __syncthreads();
     // wave 0 reserves the block's touched-list range now and writes it after
-    // its own pairs, so the reservation's latency overlaps pass 2
+    // its own runs, so that the reservation's latency overlaps them
     const uint32_t nfresh = s_nfresh;
     uint32_t fresh_base = 0;
     if (tid == 0 && nfresh) fresh_base = atomicAdd(&md.fs->n_touched.v, nfresh);
 
-    // pass 2: write the pairs, replaying the recorded walk
-    const uint32_t o = s_pair_base + off;
-    uint32_t j = 0;
-    uint32_t pos = rent[0] < (uint32_t)kWalkTable ? t_pos[rent[0]] : kNoPos;
-    uint32_t rank = rent[0] < (uint32_t)kWalkTable ? t_cnt[rent[0]] + rloc[0] : 0u;
-    uint32_t at = at0;
-    float cf[3] = {cf0[0], cf0[1], cf0[2]};
-    visit = 0;
-    for (int vi = 0; vi < nvis; ++vi) {
-        if ((kept >> vi) & 1ull) {
-            const float sd = ray_sdf(fp, ry, cf[0], cf[1], cf[2]);
-            const uint32_t voff = ((at >> 4) & 0x1C0u) | ((at >> 2) & 0x38u) | (at & 7u);
-            if (o + j < md.pair_cap)
-                md.pairs[o + j] = make_uint4(pos, rank++, (voff << kPidBits) | (fp.pid_base + (uint32_t)i),
-                                             __float_as_uint(fminf(sd, fp.tau)));
-            j++;
-        }
-        const bool ix = (stepx >> vi) & 1ull, iy = (stepy >> vi) & 1ull, iz = !ix && !iy;
-        cf[0] += ix ? sf[0] : 0.0f;
-        cf[1] += iy ? sf[1] : 0.0f;
-        cf[2] += iz ? sf[2] : 0.0f;
-        const uint32_t step = ix ? st[0] : (iy ? st[1] : st[2]);
-        at += step;
-        if ((at & kPlaceInside) != kPlaceInside) {
-            at -= 8u * step;
-            ++visit;
-            uint32_t e = kWalkTable, l = 0u;
+    if (cnt) {
 #pragma unroll
-            for (int q = 1; q < kMaxRuns; ++q) {
-                e = q == visit ? rent[q] : e;
-                l = q == visit ? rloc[q] : l;
-            }
-            pos = e < (uint32_t)kWalkTable ? t_pos[e] : kNoPos;
-            rank = e < (uint32_t)kWalkTable ? t_cnt[e] + l : 0u;
+        for (int q = 0; q < kMaxRuns; ++q) {
+            if (q > visit) continue;
+            const uint32_t e = rent[q];
+            md.ray_run[q * rcap + r] = e < (uint32_t)kWalkTable ? make_uint2(t_pos[e], t_cnt[e] + rloc[q])
+                                                                : make_uint2(kNoPos, 0u);
         }
     }
     if (tid < 64 && nfresh) {
@@ -597,10 +579,10 @@ __device__ __forceinline__ void walk_emit_block(const FrameParams &fp, const Map
     }
 }
 
-__global__ __launch_bounds__(kWalkThreads) void k_ray_walk_emit(FrameParams fp, MapDev md)
+__global__ __launch_bounds__(kWalkThreads) void k_ray_walk(FrameParams fp, MapDev md)
 {
     __shared__ WalkShared ws;
-    walk_emit_block(fp, md, blockIdx.x, ws);
+    walk_block(fp, md, blockIdx.x, blockIdx.x, ws);
 }
 
 // Map of a block of a batched launch (frame of a multi-frame pass): the last i
@@ -616,19 +598,20 @@ __device__ __forceinline__ int batch_map(const int *start, int nmaps, int blk)
     return lo;
 }
 
-__global__ __launch_bounds__(kWalkThreads) void k_ray_walk_emit_batch(MapBatch mb)
+__global__ __launch_bounds__(kWalkThreads) void k_ray_walk_batch(MapBatch mb)
 {
     __shared__ WalkShared ws;
     const int i = batch_map(mb.walk_start, mb.nmaps, blockIdx.x);
-    walk_emit_block(mb.fps[i], mb.mds[i], blockIdx.x - mb.walk_start[i], ws);
+    const int blk = blockIdx.x - mb.walk_start[i];
+    walk_block(mb.fps[i], mb.mds[i], blk, blk, ws);
 }
 
 // The rays of every frame of a multi-frame pass into one staging buffer.
-__global__ __launch_bounds__(kWalkThreads) void k_ray_walk_emit_pass(PassWalk pw, MapDev md)
+__global__ __launch_bounds__(kWalkThreads) void k_ray_walk_pass(PassWalk pw, MapDev md)
 {
     __shared__ WalkShared ws;
     const int f = batch_map(pw.blk_start, pw.nframes, blockIdx.x);
-    walk_emit_block(pw.fp[f], md, blockIdx.x - pw.blk_start[f], ws);
+    walk_block(pw.fp[f], md, blockIdx.x - pw.blk_start[f], blockIdx.x, ws);
 }
 
 // Frame (within a multi-frame pass) of sort-key point index p.
@@ -638,14 +621,6 @@ __device__ __forceinline__ int pass_frame(const FrameParams &fp, uint32_t p)
 #pragma unroll
     for (int q = 1; q < kPassFrames; ++q) f += (q < fp.nsub && p >= fp.sub_start[q]) ? 1 : 0;
     return f;
-}
-
-// Class label of the observation with sort-key point index p.
-__device__ __forceinline__ int32_t point_label(const FrameParams &fp, uint32_t p)
-{
-    if (fp.nsub <= 1) return ((const int32_t *)fp.sem)[p];
-    const int f = pass_frame(fp, p);
-    return ((const int32_t *)fp.sub_sem[f])[p - fp.sub_start[f]];
 }
 
 // ---------------------------------------------------------------------------
@@ -788,7 +763,7 @@ __global__ __launch_bounds__(256) void k_leaf_plan_batch(MapBatch mb)
 }
 
 // ---------------------------------------------------------------------------
-// 3. pair bucketing
+// 3. pairs into the leaves' buckets
 // ---------------------------------------------------------------------------
 
 // Softmax of every point's logits (max-subtracted), one lane per point, into rows
@@ -833,52 +808,106 @@ __device__ __forceinline__ void softmax_rows_range(const FrameParams &fp, const 
     }
 }
 
-__device__ __forceinline__ void pair_bucket_range(const FrameParams &fp, const MapDev &md, uint32_t blk,
-                                                  uint32_t nblk)
+// Writes the pairs of rays blk * blockDim.x + [0, blockDim.x) of a frame to their
+// leaves' buckets, one lane per ray: the recorded walk again, each kept cell's key
+// and distance (and the ray's label) at the bucket's start + rank.  All of a ray's
+// runs and bucket starts are read before the walk, side by side.  Written straight
+// to the buckets, the pairs pass through memory once; as 16-byte records in walk
+// order, bucketed by a launch of their own, an 8-sweep pass took 94 us for the walk
+// and 56 for the bucketing, now 70 and 51; 16 maps 103 and 33, now 52 and 52.
+__device__ __forceinline__ void ray_emit_block(const FrameParams &fp, const MapDev &md, int blk, int rblk)
 {
-    const uint32_t P = min(md.fs->pairs.v, md.pair_cap);
-    const uint32_t stride = nblk * blockDim.x;
+    const int i = blk * blockDim.x + threadIdx.x;
+    if (i >= fp.n) return;
+    const size_t r = (size_t)rblk * blockDim.x + threadIdx.x, rcap = md.ray_cap;
     const bool labels = fp.K > 0 && accum_path(fp);  // (the sorting leaf kernels read labels by point index)
-    // four pairs per thread and round, each step's loads issued together
-    constexpr int U = 4;
-    for (uint32_t i0 = blk * blockDim.x + threadIdx.x; i0 < P; i0 += U * stride) {
-        uint4 pq[U];  // (staging position, rank, key, distance bits)
+    // everything that does not depend on another read is requested first: the bits,
+    // the point, the label and the runs of the first three leaves (few rays visit
+    // more; a run that the walk did not write is not used)
+    constexpr int kFirst = 3;
+    const unsigned long long bits = md.ray_bits[r], stepx = md.ray_bits[rcap + r], stepy = md.ray_bits[2 * rcap + r];
+    uint2 run[kMaxRuns];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t i = i0 + u * stride;
-            pq[u] = i < P ? md.pairs[i] : make_uint4(kNoPos, 0u, 0u, 0u);
+    for (int q = 0; q < kFirst; ++q) run[q] = md.ray_run[q * rcap + r];
+    const int32_t lab = labels ? ((const int32_t *)fp.sem)[i] : 0;
+    float x, y, z;
+    load_point(fp, i, x, y, z);
+    const unsigned long long kept = bits & ((1ull << kVisitShift) - 1ull);
+    if (!kept) return;
+    const int last = (int)(bits >> kVisitShift);
+    uint32_t dst[kMaxRuns];
+#pragma unroll
+    for (int q = 0; q < kMaxRuns; ++q) {
+        if (q >= kFirst) run[q] = q <= last ? md.ray_run[q * rcap + r] : make_uint2(kNoPos, 0u);
+        dst[q] = q <= last && run[q].x != kNoPos ? (uint32_t)md.pos_plan[run[q].x].z + run[q].y : kNoPos;
+    }
+    Ray ry;
+    make_ray(fp, x, y, z, ry);
+    float cf[3], sf[3];
+    uint32_t at = 0, st[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float s = fmaf(ry.t0, ry.u[a], fp.t[a]);  // as walk_start
+        const int c = (int)floorf(s / fp.vs), up = ry.u[a] > 0.0f ? 1 : (ry.u[a] < 0.0f ? -1 : 0);
+        cf[a] = (float)c;
+        sf[a] = (float)up;
+        at |= (uint32_t)(((fp.a[a] + c) & 7) + 8) << (10 - 5 * a);
+        st[a] = (uint32_t)up << (10 - 5 * a);
+    }
+    const uint32_t pid = fp.pid_base + (uint32_t)i;
+    uint32_t d = dst[0];
+    int visit = 0;
+    for (int vi = 0; (kept >> vi) != 0ull; ++vi) {
+        if (((kept >> vi) & 1ull) && d != kNoPos) {
+            const float sd = ray_sdf(fp, ry, cf[0], cf[1], cf[2]);
+            const uint32_t voff = ((at >> 4) & 0x1C0u) | ((at >> 2) & 0x38u) | (at & 7u);
+            md.srt_kv[d] = make_uint2((voff << kPidBits) | pid, __float_as_uint(fminf(sd, fp.tau)));
+            if (labels) md.srt_lab[d] = lab;
+            ++d;
         }
-        uint32_t dst[U];
+        const bool ix = (stepx >> vi) & 1ull, iy = (stepy >> vi) & 1ull, iz = !ix && !iy;
+        cf[0] += ix ? sf[0] : 0.0f;
+        cf[1] += iy ? sf[1] : 0.0f;
+        cf[2] += iz ? sf[2] : 0.0f;
+        const uint32_t step = ix ? st[0] : (iy ? st[1] : st[2]);
+        at += step;
+        if ((at & kPlaceInside) != kPlaceInside) {
+            at -= 8u * step;
+            ++visit;
+            d = kNoPos;
 #pragma unroll
-        for (int u = 0; u < U; ++u) dst[u] = pq[u].x != kNoPos ? (uint32_t)md.pos_plan[pq[u].x].z + pq[u].y : 0u;
-        int32_t lab[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            lab[u] = labels && pq[u].x != kNoPos ? point_label(fp, pq[u].z & kPidMask) : 0;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (pq[u].x == kNoPos) continue;
-            md.srt_kv[dst[u]] = make_uint2(pq[u].z, pq[u].w);
-            // the leaf kernel's small items find the label beside the pair
-            if (labels) md.srt_lab[dst[u]] = lab[u];
+            for (int q = 1; q < kMaxRuns; ++q) d = q == visit ? dst[q] : d;
         }
     }
 }
 
 // SOFT: frames of logit rows (apart, so that the others keep their registers)
 template <bool SOFT>
-__global__ __launch_bounds__(256) void k_pair_bucket(FrameParams fp, MapDev md)
+__global__ __launch_bounds__(kWalkThreads) void k_ray_emit(FrameParams fp, MapDev md)
 {
     if constexpr (SOFT) softmax_rows_range(fp, md, blockIdx.x, gridDim.x);
-    pair_bucket_range(fp, md, blockIdx.x, gridDim.x);
+    const int n = (fp.n + kWalkThreads - 1) / kWalkThreads;
+    for (int b = blockIdx.x; b < n; b += gridDim.x) ray_emit_block(fp, md, b, b);
 }
 
-__global__ __launch_bounds__(256) void k_pair_bucket_batch(MapBatch mb)
+__global__ __launch_bounds__(kWalkThreads) void k_ray_emit_pass(PassWalk pw, MapDev md)
+{
+    const int f = batch_map(pw.blk_start, pw.nframes, blockIdx.x);
+    ray_emit_block(pw.fp[f], md, blockIdx.x - pw.blk_start[f], blockIdx.x);
+}
+
+// Blocks blk, blk + nblk, ... of a map's rays.
+__device__ __forceinline__ void ray_emit_range(const FrameParams &fp, const MapDev &md, uint32_t blk, uint32_t nblk)
+{
+    if (soft_rows(fp)) softmax_rows_range(fp, md, blk, nblk);
+    const uint32_t n = ((uint32_t)fp.n + kWalkThreads - 1) / kWalkThreads;
+    for (uint32_t b = blk; b < n; b += nblk) ray_emit_block(fp, md, (int)b, (int)b);
+}
+
+__global__ __launch_bounds__(kWalkThreads) void k_ray_emit_batch(MapBatch mb)
 {
     const int i = batch_map(mb.bucket_first, mb.nmaps, blockIdx.x);
-    const uint32_t blk = blockIdx.x - mb.bucket_first[i], nblk = mb.bucket_first[i + 1] - mb.bucket_first[i];
-    if (soft_rows(mb.fps[i])) softmax_rows_range(mb.fps[i], mb.mds[i], blk, nblk);
-    pair_bucket_range(mb.fps[i], mb.mds[i], blk, nblk);
+    ray_emit_range(mb.fps[i], mb.mds[i], blockIdx.x - mb.bucket_first[i], mb.bucket_first[i + 1] - mb.bucket_first[i]);
 }
 
 // ---------------------------------------------------------------------------
@@ -2893,7 +2922,7 @@ __device__ __noinline__ void persist_walk(const FrameParams &fpa, const MapDev &
     const MapDev &md = uni_ref(mda);
     const uint32_t b0 = uni(b0a), b1 = b0 + uni(nba);
     for (uint32_t b = b0; b < b1; ++b) {
-        walk_emit_block(fp, md, (int)b, g_ps.walk);
+        walk_block(fp, md, (int)b, (int)b, g_ps.walk);
         __syncthreads();
     }
 }
@@ -2905,8 +2934,7 @@ __device__ __noinline__ void persist_plan(const FrameParams &fp, const MapDev &m
 
 __device__ __noinline__ void persist_bucket(const FrameParams &fp, const MapDev &md, uint32_t j, uint32_t cnt)
 {
-    if (soft_rows(uni_ref(fp))) softmax_rows_range(uni_ref(fp), uni_ref(md), uni(j), uni(cnt));
-    pair_bucket_range(uni_ref(fp), uni_ref(md), uni(j), uni(cnt));
+    ray_emit_range(uni_ref(fp), uni_ref(md), uni(j), uni(cnt));
 }
 
 template <int KMAX>
@@ -3200,12 +3228,18 @@ constexpr int kBinPoints = 65536;
 
 static bool bins_large_leaves(const FrameParams &fp) { return !accum_path(fp) && fp.n > kBinPoints; }
 
-static void launch_bucket(const FrameParams &fp, const MapDev &md, const LaunchShape &shape, hipStream_t s)
+static void launch_emit(const FrameParams &fp, const MapDev &md, const LaunchShape &shape, const PassWalk *pw,
+                        hipStream_t s)
 {
-    const long long want = ((long long)fp.n * fp.maxsteps + 255) / 256;
-    const int bb = (int)std::max<long long>(1, std::min<long long>(want, shape.bucket_blocks));
-    if (soft_rows(fp)) hipLaunchKernelGGL(k_pair_bucket<true>, dim3(bb), dim3(256), 0, s, fp, md);
-    else hipLaunchKernelGGL(k_pair_bucket<false>, dim3(bb), dim3(256), 0, s, fp, md);
+    if (pw) {
+        const int nb = pw->blk_start[pw->nframes];
+        hipLaunchKernelGGL(k_ray_emit_pass, dim3(nb > 0 ? nb : 1), dim3(kWalkThreads), 0, s, *pw, md);
+    } else {
+        const int bw = (fp.n + kWalkThreads - 1) / kWalkThreads;
+        const dim3 grid(std::max(1, std::min(bw, shape.bucket_blocks)));
+        if (soft_rows(fp)) hipLaunchKernelGGL(k_ray_emit<true>, grid, dim3(kWalkThreads), 0, s, fp, md);
+        else hipLaunchKernelGGL(k_ray_emit<false>, grid, dim3(kWalkThreads), 0, s, fp, md);
+    }
     if (md.binned) {
         hipLaunchKernelGGL(k_leaf_count, dim3(4 * shape.cus), dim3(256), 0, s, md);
         hipLaunchKernelGGL(k_leaf_bin, dim3(4 * shape.cus), dim3(256), 0, s, md);
@@ -3226,16 +3260,16 @@ hipError_t launch_integrate(const FrameParams &fp, const MapDev &md_in, const La
     rec(0);
     if (pw) {
         const int nb = pw->blk_start[pw->nframes];
-        hipLaunchKernelGGL(k_ray_walk_emit_pass, dim3(nb > 0 ? nb : 1), dim3(kWalkThreads), 0, s, *pw, md);
+        hipLaunchKernelGGL(k_ray_walk_pass, dim3(nb > 0 ? nb : 1), dim3(kWalkThreads), 0, s, *pw, md);
     } else {
-        hipLaunchKernelGGL(k_ray_walk_emit, dim3(bw > 0 ? bw : 1), dim3(kWalkThreads), 0, s, fp, md);
+        hipLaunchKernelGGL(k_ray_walk, dim3(bw > 0 ? bw : 1), dim3(kWalkThreads), 0, s, fp, md);
     }
     rec(1);
     rec(2);
     hipLaunchKernelGGL(k_leaf_plan, dim3(shape.plan_blocks), dim3(256), 0, s, fp, md);
     rec(3);
     rec(4);
-    launch_bucket(fp, md, shape, s);
+    launch_emit(fp, md, shape, pw, s);
     rec(5);
     rec(6);
     const int kind = leaf_kernel_kind(fp);
@@ -3254,22 +3288,23 @@ hipError_t launch_walk(const FrameParams &fp, const MapDev &md, hipStream_t s, c
 {
     if (pw) {
         const int nb = pw->blk_start[pw->nframes];
-        hipLaunchKernelGGL(k_ray_walk_emit_pass, dim3(nb > 0 ? nb : 1), dim3(kWalkThreads), 0, s, *pw, md);
+        hipLaunchKernelGGL(k_ray_walk_pass, dim3(nb > 0 ? nb : 1), dim3(kWalkThreads), 0, s, *pw, md);
         return hipGetLastError();
     }
     const int bw = (fp.n + kWalkThreads - 1) / kWalkThreads;
-    hipLaunchKernelGGL(k_ray_walk_emit, dim3(bw > 0 ? bw : 1), dim3(kWalkThreads), 0, s, fp, md);
+    hipLaunchKernelGGL(k_ray_walk, dim3(bw > 0 ? bw : 1), dim3(kWalkThreads), 0, s, fp, md);
     return hipGetLastError();
 }
 
-hipError_t launch_after_walk(const FrameParams &fp, const MapDev &md_in, const LaunchShape &shape, hipStream_t s)
+hipError_t launch_after_walk(const FrameParams &fp, const MapDev &md_in, const LaunchShape &shape, hipStream_t s,
+                             const PassWalk *pw)
 {
     MapDev md = md_in;
     md.binned = bins_large_leaves(fp) ? 1 : 0;
     md.wave_pairs = shape.wave_pairs;
     md.slab_pairs = shape.slab_pairs;
     hipLaunchKernelGGL(k_leaf_plan, dim3(shape.plan_blocks), dim3(256), 0, s, fp, md);
-    launch_bucket(fp, md, shape, s);
+    launch_emit(fp, md, shape, pw, s);
     const int kind = leaf_kernel_kind(fp);
     launch_leaf(kind, fp, md, shape.leaf_blocks, s);
     launch_voxel_combine(kind, fp, md, combine_blocks(kind, shape), s);
@@ -3280,9 +3315,9 @@ hipError_t launch_after_walk(const FrameParams &fp, const MapDev &md_in, const L
 hipError_t launch_integrate_batched(const MapBatch &mb, const BatchPlan &plan, const LaunchShape &shape,
                                     hipStream_t s)
 {
-    hipLaunchKernelGGL(k_ray_walk_emit_batch, dim3(std::max(plan.walk_blocks, 1)), dim3(kWalkThreads), 0, s, mb);
+    hipLaunchKernelGGL(k_ray_walk_batch, dim3(std::max(plan.walk_blocks, 1)), dim3(kWalkThreads), 0, s, mb);
     hipLaunchKernelGGL(k_leaf_plan_batch, dim3(plan.plan_blocks), dim3(256), 0, s, mb);
-    hipLaunchKernelGGL(k_pair_bucket_batch, dim3(plan.bucket_blocks), dim3(256), 0, s, mb);
+    hipLaunchKernelGGL(k_ray_emit_batch, dim3(plan.bucket_blocks), dim3(kWalkThreads), 0, s, mb);
     for (int g = 0; g < plan.ngroups; ++g) {
         MapBatch sub = mb;
         sub.subset = mb.subset + plan.group_begin[g];
