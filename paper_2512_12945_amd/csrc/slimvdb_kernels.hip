@@ -1111,39 +1111,27 @@ __device__ __forceinline__ void combine_lane(const FrameParams &fp, const MapDev
     float acc[KMAX];
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) acc[k] = 0.0f;
-    // the rows of RB observations are loaded before any is used, then each is
-    // added in point order (four rows of 24 classes cost a third of the waves:
-    // 49 us against 43 with two at 65,536 rays)
-    constexpr int RB = KMAX <= 24 ? 2 : 1;
-    for (uint32_t t0 = 0; t0 < n; t0 += RB) {
-        float x[RB][KMAX];
+    // one row per lane at a time, added in point order: four workgroups per CU hide
+    // more than two rows and three workgroups do (131,071 rays, 20 classes: 56 and
+    // 65 us; four rows spill)
+    for (uint32_t q = 0; q < n; ++q) {
+        const float *row = rows + (size_t)(keys[q] & kPidMask) * stride;
+        float x[KMAX];
         if (vec) {
 #pragma unroll
-            for (int b = 0; b < RB; ++b) {
-                const float4 *row = (const float4 *)(rows + (size_t)(keys[min(t0 + b, n - 1)] & kPidMask) * stride);
-#pragma unroll
-                for (int v = 0; v < KMAX / 4; ++v) {
-                    const float4 q = 4 * v < K ? row[v] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    x[b][4 * v + 0] = q.x;
-                    x[b][4 * v + 1] = q.y;
-                    x[b][4 * v + 2] = q.z;
-                    x[b][4 * v + 3] = q.w;
-                }
+            for (int v = 0; v < KMAX / 4; ++v) {
+                const float4 f = 4 * v < K ? ((const float4 *)row)[v] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                x[4 * v + 0] = f.x;
+                x[4 * v + 1] = f.y;
+                x[4 * v + 2] = f.z;
+                x[4 * v + 3] = f.w;
             }
         } else {
 #pragma unroll
-            for (int b = 0; b < RB; ++b) {
-                const float *row = rows + (size_t)(keys[min(t0 + b, n - 1)] & kPidMask) * stride;
-#pragma unroll
-                for (int k = 0; k < KMAX; ++k) x[b][k] = k < K ? row[k] : 0.0f;
-            }
+            for (int k = 0; k < KMAX; ++k) x[k] = k < K ? row[k] : 0.0f;
         }
 #pragma unroll
-        for (int b = 0; b < RB; ++b)
-            if (t0 + b < n) {
-#pragma unroll
-                for (int k = 0; k < KMAX; ++k) acc[k] += x[b][k];
-            }
+        for (int k = 0; k < KMAX; ++k) acc[k] += x[k];
     }
     if constexpr (!early) load_record();
     // Eq. (1)-(2) with unit weights
@@ -2215,7 +2203,7 @@ __device__ __forceinline__ void leaf_fuse_range(const FrameParams &fp, const Map
 }
 
 template <int KMAX, bool WAVE, bool ROWS>
-__global__ __launch_bounds__(kLeafThreads, WAVE ? 1 : 3) void k_leaf_fuse(FrameParams fp, MapDev md)
+__global__ __launch_bounds__(kLeafThreads, WAVE ? 1 : 4) void k_leaf_fuse(FrameParams fp, MapDev md)
 {
     __shared__ LeafShared sh;
     leaf_fuse_range<KMAX, WAVE, ROWS>(fp, md, sh, blockIdx.x, gridDim.x);
@@ -2224,7 +2212,7 @@ __global__ __launch_bounds__(kLeafThreads, WAVE ? 1 : 3) void k_leaf_fuse(FrameP
 // The maps mb.subset[0 .. nsubset) of a batch, all of this kernel's kind, each
 // on its share of the grid.
 template <int KMAX, bool WAVE, bool ROWS>
-__global__ __launch_bounds__(kLeafThreads) void k_leaf_fuse_batch(MapBatch mb)
+__global__ __launch_bounds__(kLeafThreads, WAVE ? 1 : 4) void k_leaf_fuse_batch(MapBatch mb)
 {
     __shared__ LeafShared sh;
     const int q = batch_map(mb.part_first, mb.nsubset, blockIdx.x), i = mb.subset[q];
