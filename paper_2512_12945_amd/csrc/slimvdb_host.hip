@@ -100,6 +100,7 @@ struct slim_map {
     // extraction scratch
     ExtractScratch ext = {};
     uint32_t *filter = nullptr;  // the render's leaf filter
+    DevState *host_st = nullptr;  // pinned copy of the counters for the calls that read them back
     size_t ext_cap = 0;
     // kernel timing
     bool prof = false;
@@ -165,6 +166,8 @@ void free_all(slim_map *m)
     }
     for (void *p : m->allocs) (void)hipFree(p);
     m->allocs.clear();
+    if (m->host_st) (void)hipHostFree(m->host_st);
+    m->host_st = nullptr;
     for (hipEvent_t e : m->ev) (void)hipEventDestroy(e);
     m->ev.clear();
 }
@@ -338,6 +341,12 @@ slim_status slim_map_create(const slim_map_config *config, slim_map **out)
         free_all(m);
         delete m;
         return r;
+    }
+    if (hipHostMalloc((void **)&m->host_st, sizeof(DevState), hipHostMallocDefault) != hipSuccess) {
+        m->host_st = nullptr;
+        free_all(m);
+        delete m;
+        return fail(SLIM_ERR_DEVICE, "pinned allocation failed");
     }
     if (launch_reset(md, nullptr) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         free_all(m);
@@ -646,9 +655,9 @@ slim_status integrate_passes(slim_map *m, const std::vector<FrameParams> &fps, h
     }
     // whatever was queued has run once the stream drains; a pass that was not
     // applied leaves its first frame in pass_failed
-    int failed = 0;
-    HIP_OK(hipMemcpyAsync(&failed, &m->md.st->pass_failed, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipMemcpyAsync(m->host_st, m->md.st, sizeof(DevState), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
+    const int failed = m->host_st->pass_failed;
     if (failed == 0) return r;
     HIP_OK(hipMemsetAsync(&m->md.st->pass_failed, 0, sizeof(int), s));
     if (r) return r;
@@ -740,9 +749,9 @@ slim_status slim_map_stats(slim_map *m, slim_stats *out, void *stream)
     if (!out) return fail(SLIM_ERR_INVALID, "out is NULL");
     DeviceGuard g(m->cfg.device);
     hipStream_t s = (hipStream_t)stream;
-    DevState st;
-    HIP_OK(hipMemcpyAsync(&st, m->md.st, sizeof(DevState), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipMemcpyAsync(m->host_st, m->md.st, sizeof(DevState), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
+    const DevState st = *m->host_st;
     out->leaves = (int64_t)st.leaves_used;
     out->voxels = (int64_t)st.voxels_used;
     out->points_last = st.last_points;
