@@ -32,6 +32,9 @@ constexpr int kLeafLdsPairs = kLeafBatch * kLeafThreads;  // pairs a leaf holds 
 // Whole bins are dealt, so an item may hold up to a bin more; a quarter of LDS
 // is left for that.
 constexpr int kRangePairs = kLeafLdsPairs - kLeafLdsPairs / 4;
+// bits of the render's filters: leaves (32 KB), then blocks of leaves (4 KB)
+constexpr int kFilterLog2 = 18, kFilterBlockLog2 = 15;
+constexpr int kFilterWords = ((1 << kFilterLog2) + (1 << kFilterBlockLog2)) / 32;
 constexpr int kNumProfiled = 6;  // timed stages: walk, plan, bucketing, leaf kernel, voxel combine, commit
 constexpr int kAccFrames = 8;        // frames of a pass the accumulating leaf kernel takes
 constexpr int kAccWavePairs = 128;   // accumulated leaves with at most this many pairs are one wave's work
@@ -229,6 +232,7 @@ struct MapDev {
     DevState *st;
     FrameState *fs;       // the staging buffer's frame counters
     long long max_leaves, max_pages;
+    uint32_t *filter;     // kFilterWords: the render's filters
 };
 
 // Device descriptor of a batched launch over several maps (one frame each).
@@ -356,11 +360,8 @@ struct RenderParams {
     int maxsteps, width, height;
     int mode, K;           // SLIM_SEM_* and classes, for the label
 };
-// bits of the render's filters: leaves (32 KB), then blocks of leaves (4 KB)
-constexpr int kFilterLog2 = 18, kFilterBlockLog2 = 15;
-constexpr int kFilterWords = ((1 << kFilterLog2) + (1 << kFilterBlockLog2)) / 32;
-hipError_t launch_render(const MapDev &md, const RenderParams &rp, uint32_t *filter /* kFilterWords, scratch */,
-                         float *depth, int32_t *key, int32_t *label, hipStream_t s);
+hipError_t launch_render(const MapDev &md, const RenderParams &rp, float *depth, int32_t *key, int32_t *label,
+                         hipStream_t s);
 hipError_t launch_query(const MapDev &md, int nsem, float vs, const float *xyz, long long m, float *d, float *w,
                         float *sem, hipStream_t s);
 

@@ -99,7 +99,6 @@ struct slim_map {
     bool used[2] = {false, false};
     // extraction scratch
     ExtractScratch ext = {};
-    uint32_t *filter = nullptr;  // the render's leaf filter
     DevState *host_st = nullptr;  // pinned copy of the counters for the calls that read them back
     size_t ext_cap = 0;
     // kernel timing
@@ -337,7 +336,7 @@ slim_status slim_map_create(const slim_map_config *config, slim_map **out)
         (r = dalloc(m, &md.leaf_page, L * kLeafPages)) || (r = dalloc(m, &md.leaf_occ, L * kMaskWords)) ||
         (r = dalloc(m, &md.vox, NP * kPageVoxels * (size_t)md.rec_stride)) ||
         (r = dalloc(m, &md.st, 1)) ||
-        (r = dalloc(m, &md.fs, 1)) || (r = dalloc(m, &m->filter, kFilterWords))) {
+        (r = dalloc(m, &md.fs, 1)) || (r = dalloc(m, &md.filter, kFilterWords))) {
         free_all(m);
         delete m;
         return r;
@@ -941,7 +940,7 @@ slim_status slim_render(slim_map *m, const double *pose, const float *intrinsics
     rp.mode = m->cfg.sem_mode;
     rp.K = m->cfg.num_classes;
     DeviceGuard g(m->cfg.device);
-    HIP_OK(launch_render(m->md, rp, m->filter, depth, key, label, (hipStream_t)stream));
+    HIP_OK(launch_render(m->md, rp, depth, key, label, (hipStream_t)stream));
     return SLIM_OK;
 }
 

@@ -1954,9 +1954,8 @@ __device__ __forceinline__ void fuse_item(const FrameParams &fp, const MapDev &m
             }
             rank_bins(sh, sh.b_key, sh.b_val, lo, hi);
         } else {
-            // one bin larger than LDS: order it into the walk's pair buffers
-            // (consumed by the bucketing, free now), at the bin's own range of
-            // the leaf's bucket, which no other item touches
+            // one bin larger than LDS: order it into the sorted pairs' buffers, at
+            // the bin's own range of the leaf's bucket, which no other item touches
             uint32_t *bk = md.pair_key + bstart;
             float *bv = md.pair_tsdf + bstart;
             for (uint32_t t = lo + tid; t < hi; t += blockDim.x) {
@@ -3713,6 +3712,8 @@ __global__ __launch_bounds__(256) void k_reset(const MapDev md, int map)
     if (blockIdx.x == 0) {
         for (size_t i = threadIdx.x; i < sizeof(FrameState) / 4; i += blockDim.x) ((uint32_t *)md.fs)[i] = 0u;
         if (map)
+            for (size_t i = threadIdx.x; i < kFilterWords / 4; i += blockDim.x) ((uint4 *)md.filter)[i] = zero;
+        if (map)
             for (size_t i = threadIdx.x; i < sizeof(DevState) / 4; i += blockDim.x) ((uint32_t *)md.st)[i] = 0u;
     }
 }
@@ -4342,10 +4343,12 @@ hipError_t launch_predict(const MapDev &md, const PredictParams &pp, const float
 // render: first surface per pixel (the map-viewing role of Sec. III-E)
 // ---------------------------------------------------------------------------
 
-// Filters of one render: a bit per leaf, and per block of 8 x 8 x 8 leaves, taken
+// Filters of the render: a bit per leaf, and per block of 8 x 8 x 8 leaves, taken
 // at their coordinates modulo 64 leaves and 32 blocks, set for every leaf of the
 // map, so that a clear bit means that nothing is there.  A ray through empty space
-// then reads LDS instead of the leaf table.  (x, y, z: voxel keys.)
+// then reads LDS instead of the leaf table.  Every render sets the bits of all
+// leaves; none is cleared before the map is (leaves leave a map only then), so
+// renders of one map on several streams find theirs set.  (x, y, z: voxel keys.)
 __device__ __forceinline__ uint32_t leaf_bit(int x, int y, int z)
 {
     return (((uint32_t)x >> 3) & 63u) | ((((uint32_t)y >> 3) & 63u) << 6) | ((((uint32_t)z >> 3) & 63u) << 12);
@@ -4358,24 +4361,28 @@ __device__ __forceinline__ uint32_t block_bit(int x, int y, int z)
 }
 static_assert(kFilterLog2 == 18 && kFilterBlockLog2 == 15, "6 bits of each leaf coordinate, 5 of each block's");
 
-__global__ __launch_bounds__(256) void k_render_filter_clear(uint32_t *filter)
+// Bound by the atomics on one word: the leaves of a surface share few blocks, and
+// those a workgroup holds are gathered in LDS first (8,200 leaves: 24 -> 7 us).
+__global__ __launch_bounds__(256) void k_render_filter(const MapDev md)
 {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kFilterWords / 4) ((uint4 *)filter)[i] = make_uint4(0u, 0u, 0u, 0u);
-}
-
-__global__ __launch_bounds__(256) void k_render_filter(const MapDev md, uint32_t *filter)
-{
+    __shared__ uint32_t s_block[(1 << kFilterBlockLog2) / 32];
     const unsigned long long n = md.st->leaves_used;
-    for (unsigned long long i = blockIdx.x * (unsigned long long)blockDim.x + threadIdx.x; i < n;
-         i += (unsigned long long)gridDim.x * blockDim.x) {
+    const unsigned long long first = blockIdx.x * (unsigned long long)blockDim.x;
+    if (first >= n) return;
+    constexpr int kWords = (1 << kFilterBlockLog2) / 32, kBase = (1 << kFilterLog2) / 32;
+    for (int w = threadIdx.x; w < kWords; w += 256) s_block[w] = 0u;
+    __syncthreads();
+    for (unsigned long long i = first + threadIdx.x; i < n; i += (unsigned long long)gridDim.x * blockDim.x) {
         const unsigned long long k = md.leaf_key[i];
         const int x = ((int)((k >> 36) & 0x3FFFF) - kLeafBias) * 8, y = ((int)((k >> 18) & 0x3FFFF) - kLeafBias) * 8;
         const int z = ((int)(k & 0x3FFFF) - kLeafBias) * 8;
         const uint32_t b = leaf_bit(x, y, z), c = block_bit(x, y, z);
-        atomicOr(&filter[b >> 5], 1u << (b & 31));
-        atomicOr(&filter[c >> 5], 1u << (c & 31));
+        atomicOr(&md.filter[b >> 5], 1u << (b & 31));
+        atomicOr(&s_block[(c >> 5) - kBase], 1u << (c & 31));
     }
+    __syncthreads();
+    for (int w = threadIdx.x; w < kWords; w += 256)
+        if (s_block[w]) atomicOr(&md.filter[kBase + w], s_block[w]);
 }
 
 // One step of a render's walk (ties step the lowest axis): tm advances by td along
@@ -4406,19 +4413,18 @@ __device__ __forceinline__ void render_step(float &tx, float &ty, float &tz, uin
 // is the choice of the axis, three conditional additions, one to the fields and one
 // test of their upper bits; lookups and the test for the ray's end wait for the way
 // out.  In a leaf of the map 8 cells are stepped through before their occupancy, then
-// their D, are read side by side.  1209 x 448 pixels over 8,200 leaves 675 -> 420 us
-// (474 with one cell's reads at a time; 468 with 4 cells and 8 waves per SIMD).  (Jumping to the way out of
+// their D, are read side by side.  1209 x 448 pixels over 8,200 leaves 675 -> 403 us with
+// the filters' launch (474 with one cell's reads at a time; 468 with 4 cells and 8 waves per SIMD).  (Jumping to the way out of
 // an empty block in closed form, exact while tm stays in a binade, took 1,143 us: too
 // many rays are at a binade's end somewhere in the wave.)
 constexpr int kRenderThreads = 256, kRenderCells = 8;
 
 __global__ __launch_bounds__(kRenderThreads) void k_render(const MapDev md, const RenderParams rp,
-                                                           const uint32_t *filter, float *depth, int32_t *key,
-                                                           int32_t *label)
+                                                           float *depth, int32_t *key, int32_t *label)
 {
     __shared__ uint32_t s_filter[kFilterWords];
     for (int i = threadIdx.x; i < kFilterWords / 4; i += kRenderThreads)
-        ((uint4 *)s_filter)[i] = ((const uint4 *)filter)[i];
+        ((uint4 *)s_filter)[i] = ((const uint4 *)md.filter)[i];
     __syncthreads();
     // 4 waves of 8 x 8 pixels
     const int lane = lane_id(), wv = threadIdx.x >> 6;
@@ -4595,14 +4601,13 @@ __global__ __launch_bounds__(kRenderThreads) void k_render(const MapDev md, cons
     if (label) label[i] = out_l;
 }
 
-hipError_t launch_render(const MapDev &md, const RenderParams &rp, uint32_t *filter, float *depth, int32_t *key,
-                         int32_t *label, hipStream_t s)
+hipError_t launch_render(const MapDev &md, const RenderParams &rp, float *depth, int32_t *key, int32_t *label,
+                         hipStream_t s)
 {
     if (rp.width <= 0 || rp.height <= 0) return hipGetLastError();
-    hipLaunchKernelGGL(k_render_filter_clear, dim3((kFilterWords / 4 + 255) / 256), dim3(256), 0, s, filter);
-    hipLaunchKernelGGL(k_render_filter, dim3(256), dim3(256), 0, s, md, filter);
+    hipLaunchKernelGGL(k_render_filter, dim3(256), dim3(256), 0, s, md);
     const dim3 grid((rp.width + 31) / 32, (rp.height + 7) / 8);
-    hipLaunchKernelGGL(k_render, grid, dim3(kRenderThreads), 0, s, md, rp, filter, depth, key, label);
+    hipLaunchKernelGGL(k_render, grid, dim3(kRenderThreads), 0, s, md, rp, depth, key, label);
     return hipGetLastError();
 }
 

@@ -91,3 +91,42 @@ def test_render_partial_tiles_and_far_maps(W, H, shift):
     assert np.all(np.abs(gd[both] - od[both]) <= 2e-6 * od[both] + 1e-5 * tau * np.sqrt(3.0) * vs / oout["margin"][both]
                   + 1e-6)
     assert both.sum() >= (1 if W == 1 else W * H // 4)
+
+
+def test_render_again_after_growth_and_reset():
+    """A map rendered, grown, rendered, reset and filled elsewhere: every image is that of a map which was never
+    rendered before, bit for bit, and that of the emptied map holds no surface."""
+    frames = synth.room_sequence(4, seed=9, yaw_span=2.0, width=64, height=48, f=53.3, cx=32.0, cy=24.0)
+
+    def fill(m, first, last, shift):
+        for fr in frames[first:last]:
+            pose = fr["pose"].copy()
+            pose[:3, 3] += shift
+            m.integrate(torch.from_numpy(fr["points"]).cuda(), pose, torch.from_numpy(fr["label"]).cuda(), sv.IN_LABEL_I32)
+
+    def image(m, shift):
+        pose = synth.pose_matrix(synth.camera_rotation((1.0, 0.2, 0.0)), np.array([2.0, 2.0, 1.4]) + shift)
+        return m.render(pose, (40.0, 40.0, 32.0, 24.0), 64, 48, 0.05, 8.0)
+
+    def new():
+        return sv.Map(0.05, 0.15, 0.0, 100.0, sv.SEM_CLOSED, 5, 0, 0, 1 << 14, 1 << 20)
+
+    def check(got, steps, shift):
+        fresh = new()
+        for s in steps:
+            fill(fresh, *s)
+        want = image(fresh, shift)
+        for k in want:
+            assert torch.equal(got[k].view(torch.int32), want[k].view(torch.int32)), k
+        return torch.isfinite(got["depth"]).sum().item()
+
+    g, here, there = new(), np.zeros(3), np.array([55.0, -31.0, 7.0])
+    fill(g, 0, 1, here)
+    assert check(image(g, here), [(0, 1, here)], here) > 100
+    fill(g, 1, 4, here)
+    assert check(image(g, here), [(0, 1, here), (1, 4, here)], here) > 100
+    g.reset()
+    assert not torch.isfinite(image(g, here)["depth"]).any()
+    fill(g, 0, 4, there)
+    assert check(image(g, there), [(0, 4, there)], there) > 100
+    assert not torch.isfinite(image(g, here)["depth"]).any()
