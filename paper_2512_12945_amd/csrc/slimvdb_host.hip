@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "slim_internal.h"
@@ -99,7 +100,9 @@ struct slim_map {
     bool used[2] = {false, false};
     // extraction scratch
     ExtractScratch ext = {};
-    DevState *host_st = nullptr;  // pinned copy of the counters for the calls that read them back
+    // pinned copy of the counters for the calls that read them back, one at a time
+    DevState *host_st = nullptr;
+    std::mutex host_lock;
     size_t ext_cap = 0;
     // kernel timing
     bool prof = false;
@@ -593,6 +596,16 @@ void make_pass(const std::vector<FrameParams> &fps, int t0, int t1, FrameParams 
     base->n = (int)off;
 }
 
+// The map's counters once the work queued on s has run.
+slim_status read_state(slim_map *m, hipStream_t s, DevState *out)
+{
+    std::lock_guard<std::mutex> one(m->host_lock);
+    HIP_OK(hipMemcpyAsync(m->host_st, m->md.st, sizeof(DevState), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    *out = *m->host_st;
+    return SLIM_OK;
+}
+
 // A sequence in passes of up to m->pass_frames consecutive frames (the last
 // frame alone, so that the per-frame statistics are its own).  Without kernel
 // timing, passes alternate between the two staging buffers and the walk of
@@ -654,9 +667,9 @@ slim_status integrate_passes(slim_map *m, const std::vector<FrameParams> &fps, h
     }
     // whatever was queued has run once the stream drains; a pass that was not
     // applied leaves its first frame in pass_failed
-    HIP_OK(hipMemcpyAsync(m->host_st, m->md.st, sizeof(DevState), hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
-    const int failed = m->host_st->pass_failed;
+    DevState st;
+    if (slim_status e = read_state(m, s, &st)) return e;
+    const int failed = st.pass_failed;
     if (failed == 0) return r;
     HIP_OK(hipMemsetAsync(&m->md.st->pass_failed, 0, sizeof(int), s));
     if (r) return r;
@@ -748,9 +761,8 @@ slim_status slim_map_stats(slim_map *m, slim_stats *out, void *stream)
     if (!out) return fail(SLIM_ERR_INVALID, "out is NULL");
     DeviceGuard g(m->cfg.device);
     hipStream_t s = (hipStream_t)stream;
-    HIP_OK(hipMemcpyAsync(m->host_st, m->md.st, sizeof(DevState), hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
-    const DevState st = *m->host_st;
+    DevState st;
+    if (slim_status e = read_state(m, s, &st)) return e;
     out->leaves = (int64_t)st.leaves_used;
     out->voxels = (int64_t)st.voxels_used;
     out->points_last = st.last_points;
