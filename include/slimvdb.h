@@ -172,8 +172,8 @@ slim_status slim_extract(slim_map *map, int64_t capacity, int32_t *keys_dev, flo
 /* As slim_extract, for callers that cannot allocate device memory (code around
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same arguments, outputs and errors, and it calls no hipMalloc, hipFree or
- * other allocating routine.  Its per-leaf scratch (28 bytes a leaf) is a
- * fixed device array of the library of 28 MiB, one per GPU, held until the
+ * other allocating routine.  Its per-leaf scratch (16 bytes a leaf) is a
+ * fixed device array of the library of 16 MiB, one per GPU, held until the
  * process ends; a map with more than SLIM_EXTRACT_NOALLOC_MAX_LEAVES leaves is
  * refused with SLIM_ERR_CAPACITY before anything is queued.  Every call on one
  * GPU shares that array: calls that overlap on one GPU (several host threads,

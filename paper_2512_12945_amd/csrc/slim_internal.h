@@ -324,16 +324,14 @@ hipError_t launch_loss(const FrameParams &fp, const MapDev &md, const LossParams
 hipError_t launch_backward(const FrameParams &fp, const MapDev &md, const LossParams &lp, const float *grad_scale,
                            float *grad_logits, float *grad_ranges, hipStream_t s);
 constexpr int kLossThreads = 256;
-// Per-leaf scratch of an export: packed keys and slots, two of each, and voxel
-// offsets.
+// Per-leaf scratch of an export: two arrays of packed keys, the last written of
+// which ends as slots and voxel offsets.
 struct ExtractScratch {
     unsigned long long *keys, *keys2;
-    int32_t *slots, *slots2;
-    uint32_t *offsets;
 };
 hipError_t launch_extract(const MapDev &md, int nsem, long long nleaves, const ExtractScratch &x, int32_t *keys,
                           float *d, float *w, float *sem, hipStream_t s);
-// Allocation-free extract: its per-leaf scratch (28 bytes) lives in a file-scope
+// Allocation-free extract: its per-leaf scratch (16 bytes) lives in a file-scope
 // device array of the library, one copy per GPU, for at most kNoAllocMaxLeaves
 // leaves.
 constexpr long long kNoAllocMaxLeaves = 1ll << 20;

@@ -803,8 +803,7 @@ slim_status slim_extract(slim_map *m, int64_t capacity, int32_t *keys, float *d,
     hipStream_t s = (hipStream_t)stream;
     if ((size_t)st.leaves > m->ext_cap) {
         HIP_OK(hipStreamSynchronize(s));
-        for (void *p : {(void *)m->ext.keys, (void *)m->ext.keys2, (void *)m->ext.slots, (void *)m->ext.slots2,
-                        (void *)m->ext.offsets}) {
+        for (void *p : {(void *)m->ext.keys, (void *)m->ext.keys2}) {
             if (!p) continue;
             (void)hipFree(p);
             m->allocs.erase(std::remove(m->allocs.begin(), m->allocs.end(), p), m->allocs.end());
@@ -812,10 +811,7 @@ slim_status slim_extract(slim_map *m, int64_t capacity, int32_t *keys, float *d,
         m->ext = {};
         m->ext_cap = 0;
         const size_t cap = (size_t)st.leaves;
-        if ((r = dalloc(m, &m->ext.keys, cap)) || (r = dalloc(m, &m->ext.keys2, cap)) ||
-            (r = dalloc(m, &m->ext.slots, cap)) || (r = dalloc(m, &m->ext.slots2, cap)) ||
-            (r = dalloc(m, &m->ext.offsets, cap)))
-            return r;
+        if ((r = dalloc(m, &m->ext.keys, cap)) || (r = dalloc(m, &m->ext.keys2, cap))) return r;
         m->ext_cap = cap;
     }
     HIP_OK(launch_extract(m->md, m->nsem, st.leaves, m->ext, keys, d, w, m->nsem ? sem : nullptr, s));
@@ -852,9 +848,6 @@ slim_status slim_extract_noalloc(slim_map *m, int64_t capacity, int32_t *keys, f
     ExtractScratch x;
     x.keys = (unsigned long long *)ptr;
     x.keys2 = x.keys + kNoAllocMaxLeaves;
-    x.slots = (int32_t *)(x.keys2 + kNoAllocMaxLeaves);
-    x.slots2 = x.slots + kNoAllocMaxLeaves;
-    x.offsets = (uint32_t *)(x.slots2 + kNoAllocMaxLeaves);
     HIP_OK(launch_extract(m->md, m->nsem, st.leaves, x, keys, d, w, m->nsem ? sem : nullptr, s));
     HIP_OK(hipStreamSynchronize(s));
     return SLIM_OK;

@@ -3789,34 +3789,36 @@ static uint32_t row_div(uint32_t per) { return per > 1 ? (uint32_t)((1ull << 32)
 // network, two leaves per thread), then merged kMergeRuns runs at a time by rank:
 // a leaf's place is its place in its own run plus, for each other run, the number
 // of smaller keys there, found by binary searches that advance together (keys are
-// distinct).  The last of these launches also counts each leaf's voxels.
-// 11,500 leaves: two launches of 26 and 17 us instead of 105 compare-exchange launches
-// of 2.4 us each.
+// distinct).  Only keys are moved: the last of these launches finds each leaf's slot in
+// the leaf table and counts its voxels (the slots moved beside the keys took 28 bytes of
+// scratch a leaf instead of 16, and the same time).  11,500 leaves: two launches of 26
+// and 17 us instead of 105 compare-exchange launches of 2.4 us each.
 constexpr int kSortRun = 2048, kMergeRuns = 8;
 
-__device__ __forceinline__ uint32_t leaf_voxels(const MapDev &md, int32_t slot)
+// A leaf's slot and its number of voxels.
+__device__ __forceinline__ uint2 leaf_entry(const MapDev &md, unsigned long long key)
 {
+    const int slot = map_find(md, key);
+    if (slot < 0) return make_uint2(0u, 0u);  // (every leaf of the map is in its table)
     uint32_t c = 0;
 #pragma unroll
     for (int w = 0; w < kMaskWords / 4; ++w) {
         const uint4 o = ((const uint4 *)md.leaf_occ)[(size_t)slot * (kMaskWords / 4) + w];
         c += __popc(o.x) + __popc(o.y) + __popc(o.z) + __popc(o.w);
     }
-    return c;
+    return make_uint2((uint32_t)slot, c);
 }
 
+// leaves: the entries in key order where one run is all (or null)
 __global__ __launch_bounds__(kSortRun / 2) void k_leaf_sort(const MapDev md, long long nleaves, unsigned long long *keys,
-                                                            int32_t *slots, uint32_t *counts)
+                                                            uint2 *leaves)
 {
     __shared__ unsigned long long k[kSortRun];
-    __shared__ int32_t v[kSortRun];
     const long long base = (long long)blockIdx.x * kSortRun;
     const int t = threadIdx.x;
 #pragma unroll
-    for (int q = t; q < kSortRun; q += kSortRun / 2) {
+    for (int q = t; q < kSortRun; q += kSortRun / 2)
         k[q] = base + q < nleaves ? md.leaf_key[base + q] : kEmptyKey;  // (above every key)
-        v[q] = (int32_t)(base + q);
-    }
     // a step over spans of at most 128 places stays inside the 128 that a wave's
     // lanes compare, so only the wider steps (10 of 66) need the whole workgroup
     int before = kSortRun;
@@ -3833,24 +3835,21 @@ __global__ __launch_bounds__(kSortRun / 2) void k_leaf_sort(const MapDev md, lon
             if (kb < ka) {
                 k[a] = kb;
                 k[b] = ka;
-                const int32_t x = v[a];
-                v[a] = v[b];
-                v[b] = x;
             }
         }
     __syncthreads();
 #pragma unroll
     for (int q = t; q < kSortRun; q += kSortRun / 2)
         if (base + q < nleaves) {
-            keys[base + q] = k[q];
-            slots[base + q] = v[q];
-            if (counts) counts[base + q] = leaf_voxels(md, v[q]);
+            if (leaves) leaves[base + q] = leaf_entry(md, k[q]);
+            else keys[base + q] = k[q];
         }
 }
 
+// leaves: the entries in key order from the last merge (or null)
 __global__ __launch_bounds__(256) void k_leaf_merge(const MapDev md, long long nleaves, long long run,
-                                                    const unsigned long long *keys, const int32_t *slots,
-                                                    unsigned long long *keys_out, int32_t *slots_out, uint32_t *counts)
+                                                    const unsigned long long *keys, unsigned long long *keys_out,
+                                                    uint2 *leaves)
 {
     const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     if (i >= nleaves) return;
@@ -3876,15 +3875,13 @@ __global__ __launch_bounds__(256) void k_leaf_merge(const MapDev md, long long n
     long long out = i - own * run;  // group + place in the own run
 #pragma unroll
     for (int q = 0; q < kMergeRuns; ++q) out += pos[q];
-    const int32_t slot = slots[i];
-    keys_out[out] = key;
-    slots_out[out] = slot;
-    if (counts) counts[out] = leaf_voxels(md, slot);
+    if (leaves) leaves[out] = leaf_entry(md, key);
+    else keys_out[out] = key;
 }
 
 // Exclusive prefix sum of the leaves' voxel counts, in place, by one workgroup
 // (16 counts per thread and round: 11,500 leaves are one round).
-__global__ __launch_bounds__(1024) void k_leaf_offsets(long long nleaves, uint32_t *counts)
+__global__ __launch_bounds__(1024) void k_leaf_offsets(long long nleaves, uint2 *leaves)
 {
     __shared__ uint32_t wsum[16];
     constexpr int U = 16;
@@ -3894,7 +3891,7 @@ __global__ __launch_bounds__(1024) void k_leaf_offsets(long long nleaves, uint32
         uint32_t c[U], t = 0;
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            c[q] = i + q < nleaves ? counts[i + q] : 0u;
+            c[q] = i + q < nleaves ? leaves[i + q].y : 0u;
             t += c[q];
         }
         const uint32_t incl = wave_incl_scan(t);
@@ -3908,7 +3905,7 @@ __global__ __launch_bounds__(1024) void k_leaf_offsets(long long nleaves, uint32
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            if (i + q < nleaves) counts[i + q] = run;
+            if (i + q < nleaves) leaves[i + q].y = run;
             run += c[q];
         }
         carry += total;
@@ -3923,17 +3920,17 @@ __global__ __launch_bounds__(1024) void k_leaf_offsets(long long nleaves, uint32
 // voxel copied its row alone before).
 template <int W>
 __global__ __launch_bounds__(256) void k_extract(const MapDev md, long long nleaves, uint32_t nsem, uint32_t div,
-                                                 const unsigned long long *lkeys, const int32_t *slots,
-                                                 const uint32_t *offsets, int32_t *keys, float *d, float *w, float *sem)
+                                                 const uint2 *leaves, int32_t *keys, float *d, float *w, float *sem)
 {
     __shared__ uint32_t occ[kMaskWords];
     __shared__ int pages[kLeafPages];
     __shared__ int recs[kLeafVoxels];
     const int tid = threadIdx.x;
     for (long long j = blockIdx.x; j < nleaves; j += gridDim.x) {
-        const int slot = slots[j];
-        const unsigned long long lk = lkeys[j];
-        const size_t first = offsets[j];
+        const uint2 leaf = leaves[j];
+        const int slot = (int)leaf.x;
+        const unsigned long long lk = md.leaf_key[slot];
+        const size_t first = leaf.y;
         if (tid < kMaskWords) occ[tid] = md.leaf_occ[(size_t)slot * kMaskWords + tid];
         if (tid < kLeafPages) pages[tid] = md.leaf_page[(size_t)slot * kLeafPages + tid];
         __syncthreads();
@@ -3994,31 +3991,31 @@ hipError_t launch_extract(const MapDev &md, int nsem, long long nleaves, const E
 {
     if (nleaves <= 0) return hipGetLastError();
     unsigned long long *ka = x.keys, *kb = x.keys2;
-    int32_t *sa = x.slots, *sb = x.slots2;
+    uint2 *leaves = nleaves <= kSortRun ? (uint2 *)ka : nullptr;
     hipLaunchKernelGGL(k_leaf_sort, dim3((unsigned)((nleaves + kSortRun - 1) / kSortRun)), dim3(kSortRun / 2), 0, s, md,
-                       nleaves, ka, sa, nleaves <= kSortRun ? x.offsets : nullptr);
+                       nleaves, ka, leaves);
     for (long long run = kSortRun; run < nleaves; run *= kMergeRuns) {
+        if (run * kMergeRuns >= nleaves) leaves = (uint2 *)kb;
         hipLaunchKernelGGL(k_leaf_merge, dim3((unsigned)((nleaves + 255) / 256)), dim3(256), 0, s, md, nleaves, run, ka,
-                           sa, kb, sb, run * kMergeRuns >= nleaves ? x.offsets : nullptr);
+                           kb, leaves);
         std::swap(ka, kb);
-        std::swap(sa, sb);
     }
-    hipLaunchKernelGGL(k_leaf_offsets, dim3(1), dim3(1024), 0, s, nleaves, x.offsets);
+    hipLaunchKernelGGL(k_leaf_offsets, dim3(1), dim3(1024), 0, s, nleaves, leaves);
     const uint32_t n = sem ? (uint32_t)nsem : 0u;
     const bool pair = n % 2 == 0 && ((uintptr_t)sem & 7u) == 0;
     const dim3 grid((unsigned)std::min<long long>(nleaves, 16384)), block(256);
-    if (n == 0) hipLaunchKernelGGL(k_extract<0>, grid, block, 0, s, md, nleaves, n, 0u, ka, sa, x.offsets, keys, d, w, sem);
-    else if (pair) hipLaunchKernelGGL(k_extract<2>, grid, block, 0, s, md, nleaves, n, row_div(n / 2), ka, sa, x.offsets, keys, d, w, sem);
-    else hipLaunchKernelGGL(k_extract<1>, grid, block, 0, s, md, nleaves, n, row_div(n), ka, sa, x.offsets, keys, d, w, sem);
+    if (n == 0) hipLaunchKernelGGL(k_extract<0>, grid, block, 0, s, md, nleaves, n, 0u, leaves, keys, d, w, sem);
+    else if (pair) hipLaunchKernelGGL(k_extract<2>, grid, block, 0, s, md, nleaves, n, row_div(n / 2), leaves, keys, d, w, sem);
+    else hipLaunchKernelGGL(k_extract<1>, grid, block, 0, s, md, nleaves, n, row_div(n), leaves, keys, d, w, sem);
     return hipGetLastError();
 }
 
-// Scratch of the allocation-free extract (slim_extract_noalloc): the leaves'
-// keys and slots, twice (a merge reads one and writes the other), and their
-// voxel offsets, for at most kNoAllocMaxLeaves leaves.  Each GPU the library runs on holds its own copy
+// Scratch of the allocation-free extract (slim_extract_noalloc): two arrays of
+// leaf keys (a merge reads one and writes the other), for at most
+// kNoAllocMaxLeaves leaves.  Each GPU the library runs on holds its own copy
 // until the process ends.  In host code `scratch` names a host-side stand-in:
 // kernels get the device address that noalloc_scratch_setup resolved.
-static __device__ __align__(256) unsigned char scratch[kNoAllocMaxLeaves * 28];
+static __device__ __align__(256) unsigned char scratch[kNoAllocMaxLeaves * 16];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -4414,7 +4411,8 @@ __device__ __forceinline__ void render_step(float &tx, float &ty, float &tz, uin
 // test of their upper bits; lookups and the test for the ray's end wait for the way
 // out.  In a leaf of the map 8 cells are stepped through before their occupancy, then
 // their D, are read side by side.  1209 x 448 pixels over 8,200 leaves 675 -> 403 us with
-// the filters' launch (474 with one cell's reads at a time; 468 with 4 cells and 8 waves per SIMD).  (Jumping to the way out of
+// the filters' launch (before that launch was 24 us shorter: 420, 474 with one cell's
+// reads at a time, 468 with 4 cells and 8 waves per SIMD).  (Jumping to the way out of
 // an empty block in closed form, exact while tm stays in a binade, took 1,143 us: too
 // many rays are at a binade's end somewhere in the wave.)
 constexpr int kRenderThreads = 256, kRenderCells = 8;
