@@ -4411,8 +4411,8 @@ __device__ __forceinline__ void render_step(float &tx, float &ty, float &tz, uin
 // test of their upper bits; lookups and the test for the ray's end wait for the way
 // out.  In a leaf of the map 8 cells are stepped through before their occupancy, then
 // their D, are read side by side.  1209 x 448 pixels over 8,200 leaves 675 -> 403 us with
-// the filters' launch (before that launch was 24 us shorter: 420, 474 with one cell's
-// reads at a time, 468 with 4 cells and 8 waves per SIMD).  (Jumping to the way out of
+// the filters' launch (with the filters cleared and built by two launches 420, then 474
+// with one cell's reads at a time, 468 with 4 cells and 8 waves per SIMD).  (Jumping to the way out of
 // an empty block in closed form, exact while tm stays in a binade, took 1,143 us: too
 // many rays are at a binade's end somewhere in the wave.)
 constexpr int kRenderThreads = 256, kRenderCells = 8;
