@@ -4188,128 +4188,130 @@ __global__ __launch_bounds__(256, PMAX <= 128 ? 6 : 1) void k_predict_open(const
     __shared__ float n2s[4][TQ], q2s[4][PC];
     const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6, g = lane >> 4, c = lane & 15;
     const int L = pp.L, P = pp.P;
-    const long long q0 = blockIdx.x * (long long)TQ;
-    // lane c of every 16 holds the record of point c
-    const long long qc = q0 + c;
-    const int rec = qc < m ? (int)lookup_point(md, pp.vs, xyz[3 * qc], xyz[3 * qc + 1], xyz[3 * qc + 2]) : -1;
-    const float *A = md.vox + (size_t)(rec >= 0 ? rec : 0) * md.rec_stride + 2;
-    for (int p0 = 0; p0 < P; p0 += PC) {
-        f32x4_t acc[CT];
-        float n2 = 0.0f, q2[CT];
-#pragma unroll
-        for (int u = 0; u < CT; ++u) {
-            q2[u] = 0.0f;
-            acc[u] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-#pragma unroll 2
-        for (int s = w; 16 * s < L; s += 4) {
-            const int k = 16 * s + 4 * g;
-            float a[4], b[CT][4];
-            if constexpr (FAST) {
-                const float2 x = rec >= 0 ? *(const float2 *)(A + k) : make_float2(0.0f, 0.0f);
-                const float2 y = rec >= 0 ? *(const float2 *)(A + k + 2) : make_float2(0.0f, 0.0f);
-                a[0] = x.x; a[1] = x.y; a[2] = y.x; a[3] = y.y;
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a[j] = rec >= 0 && k + j < L ? A[k + j] : 0.0f;
-            }
-#pragma unroll
+    for (long long q0 = blockIdx.x * (long long)TQ; q0 < m; q0 += gridDim.x * (long long)TQ) {
+        // lane c of every 16 holds the record of point c
+        const long long qc = q0 + c;
+        const int rec = qc < m ? (int)lookup_point(md, pp.vs, xyz[3 * qc], xyz[3 * qc + 1], xyz[3 * qc + 2]) : -1;
+        const float *A = md.vox + (size_t)(rec >= 0 ? rec : 0) * md.rec_stride + 2;
+        for (int p0 = 0; p0 < P; p0 += PC) {
+            f32x4_t acc[CT];
+            float n2 = 0.0f, q2[CT];
+    #pragma unroll
             for (int u = 0; u < CT; ++u) {
-                const int p = p0 + 16 * u + c;
-                const float *B = pp.protos + (size_t)(p < P ? p : 0) * L + k;
+                q2[u] = 0.0f;
+                acc[u] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+    #pragma unroll 2
+            for (int s = w; 16 * s < L; s += 4) {
+                const int k = 16 * s + 4 * g;
+                float a[4], b[CT][4];
                 if constexpr (FAST) {
-                    const float4 x = p < P ? *(const float4 *)B : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    b[u][0] = x.x; b[u][1] = x.y; b[u][2] = x.z; b[u][3] = x.w;
+                    const float2 x = rec >= 0 ? *(const float2 *)(A + k) : make_float2(0.0f, 0.0f);
+                    const float2 y = rec >= 0 ? *(const float2 *)(A + k + 2) : make_float2(0.0f, 0.0f);
+                    a[0] = x.x; a[1] = x.y; a[2] = y.x; a[3] = y.y;
                 } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) b[u][j] = p < P && k + j < L ? B[j] : 0.0f;
+    #pragma unroll
+                    for (int j = 0; j < 4; ++j) a[j] = rec >= 0 && k + j < L ? A[k + j] : 0.0f;
                 }
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                n2 += a[j] * a[j];
-#pragma unroll
+    #pragma unroll
                 for (int u = 0; u < CT; ++u) {
-                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[u][j], acc[u], 0, 0, 0);
-                    q2[u] += b[u][j] * b[u][j];
+                    const int p = p0 + 16 * u + c;
+                    const float *B = pp.protos + (size_t)(p < P ? p : 0) * L + k;
+                    if constexpr (FAST) {
+                        const float4 x = p < P ? *(const float4 *)B : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                        b[u][0] = x.x; b[u][1] = x.y; b[u][2] = x.z; b[u][3] = x.w;
+                    } else {
+    #pragma unroll
+                        for (int j = 0; j < 4; ++j) b[u][j] = p < P && k + j < L ? B[j] : 0.0f;
+                    }
+                }
+    #pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    n2 += a[j] * a[j];
+    #pragma unroll
+                    for (int u = 0; u < CT; ++u) {
+                        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[u][j], acc[u], 0, 0, 0);
+                        q2[u] += b[u][j] * b[u][j];
+                    }
                 }
             }
-        }
-        n2 += __shfl_xor(n2, 16, 64);
-        n2 += __shfl_xor(n2, 32, 64);
-        if (g == 0) n2s[w][c] = n2;
-#pragma unroll
-        for (int u = 0; u < CT; ++u)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) part[w][4 * g + r][16 * u + c] = acc[u][r];
-#pragma unroll
-        for (int u = 0; u < CT; ++u) {
-            q2[u] += __shfl_xor(q2[u], 16, 64);
-            q2[u] += __shfl_xor(q2[u], 32, 64);
-            if (g == 0) q2s[w][16 * u + c] = q2[u];
-        }
-        __syncthreads();
-        // cosine similarity of the predictive mean with every prototype
-        for (int e = tid; e < TQ * PC; e += 256) {
-            const int i = e / PC, j = e % PC;
-            if (p0 + j >= P) continue;
-            const float dot = (part[0][i][j] + part[1][i][j]) + (part[2][i][j] + part[3][i][j]);
-            const float nm = sqrtf((n2s[0][i] + n2s[1][i]) + (n2s[2][i] + n2s[3][i]));
-            const float nq = sqrtf((q2s[0][j] + q2s[1][j]) + (q2s[2][j] + q2s[3][j]));
-            sims[i][p0 + j] = dot / (nm * nq) * pp.inv_temp;
-        }
-        __syncthreads();
-    }
-    // wave w's points: w, w + 4, w + 8, w + 12
-    if (var && pp.mode == SLIM_SEM_OPEN) {
-        // Eq. (15) with lambda = 2 nu = W: variance 2 beta (W + 1) / (W (W - 2)) for W > 2
-        float W[4];
-        const float *B[4];
-        float *out[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int i = w + 4 * t, r = __shfl(rec, i, 64);
-            const float *R = md.vox + (size_t)(r >= 0 ? r : 0) * md.rec_stride;
-            W[t] = r >= 0 ? R[1] : 0.0f;
-            B[t] = R + 2 + L;
-            out[t] = q0 + i < m ? var + (size_t)(q0 + i) * L : nullptr;
-        }
-#pragma unroll 2
-        for (int d = lane; d < L; d += 64) {
-            float x[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) x[t] = W[t] > 2.0f ? B[t][d] : 0.0f;
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (out[t]) out[t][d] = W[t] > 2.0f ? 2.0f * x[t] * (W[t] + 1.0f) / (W[t] * (W[t] - 2.0f)) : NAN;
-        }
-    }
-    for (int i = w; i < TQ && q0 + i < m; i += 4) {
-        const long long q = q0 + i;
-        const float *S = sims[i];
-        const bool has = __shfl(rec, i, 64) >= 0;
-        float best = -INFINITY;
-        int arg = 0x7FFFFFFF;
-        if (has) {
-            float mx = -INFINITY;
-            for (int j = lane; j < P; j += 64) mx = fmaxf(mx, S[j]);
-            mx = wave_max(mx);
-            float es = 0.0f;
-            for (int j = lane; j < P; j += 64) es += expf(S[j] - mx);
-            const float den = wave_sum(es);
-            for (int j = lane; j < P; j += 64) {
-                const float p = expf(S[j] - mx) / den;
-                if (prob) prob[q * P + j] = p;
-                if (p > best) {
-                    best = p;
-                    arg = j;
-                }
+            n2 += __shfl_xor(n2, 16, 64);
+            n2 += __shfl_xor(n2, 32, 64);
+            if (g == 0) n2s[w][c] = n2;
+    #pragma unroll
+            for (int u = 0; u < CT; ++u)
+    #pragma unroll
+                for (int r = 0; r < 4; ++r) part[w][4 * g + r][16 * u + c] = acc[u][r];
+    #pragma unroll
+            for (int u = 0; u < CT; ++u) {
+                q2[u] += __shfl_xor(q2[u], 16, 64);
+                q2[u] += __shfl_xor(q2[u], 32, 64);
+                if (g == 0) q2s[w][16 * u + c] = q2[u];
             }
-        } else if (prob) {
-            for (int j = lane; j < P; j += 64) prob[q * P + j] = 0.0f;
+            __syncthreads();
+            // cosine similarity of the predictive mean with every prototype
+            for (int e = tid; e < TQ * PC; e += 256) {
+                const int i = e / PC, j = e % PC;
+                if (p0 + j >= P) continue;
+                const float dot = (part[0][i][j] + part[1][i][j]) + (part[2][i][j] + part[3][i][j]);
+                const float nm = sqrtf((n2s[0][i] + n2s[1][i]) + (n2s[2][i] + n2s[3][i]));
+                const float nq = sqrtf((q2s[0][j] + q2s[1][j]) + (q2s[2][j] + q2s[3][j]));
+                sims[i][p0 + j] = dot / (nm * nq) * pp.inv_temp;
+            }
+            __syncthreads();
         }
-        wave_argmax(best, arg);
-        if (label && lane == 0) label[q] = (has && best >= pp.threshold) ? arg : -1;
+        // wave w's points: w, w + 4, w + 8, w + 12
+        if (var && pp.mode == SLIM_SEM_OPEN) {
+            // Eq. (15) with lambda = 2 nu = W: variance 2 beta (W + 1) / (W (W - 2)) for W > 2
+            float W[4];
+            const float *B[4];
+            float *out[4];
+    #pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int i = w + 4 * t, r = __shfl(rec, i, 64);
+                const float *R = md.vox + (size_t)(r >= 0 ? r : 0) * md.rec_stride;
+                W[t] = r >= 0 ? R[1] : 0.0f;
+                B[t] = R + 2 + L;
+                out[t] = q0 + i < m ? var + (size_t)(q0 + i) * L : nullptr;
+            }
+    #pragma unroll 2
+            for (int d = lane; d < L; d += 64) {
+                float x[4];
+    #pragma unroll
+                for (int t = 0; t < 4; ++t) x[t] = W[t] > 2.0f ? B[t][d] : 0.0f;
+    #pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (out[t]) out[t][d] = W[t] > 2.0f ? 2.0f * x[t] * (W[t] + 1.0f) / (W[t] * (W[t] - 2.0f)) : NAN;
+            }
+        }
+        for (int i = w; i < TQ && q0 + i < m; i += 4) {
+            const long long q = q0 + i;
+            const float *S = sims[i];
+            const bool has = __shfl(rec, i, 64) >= 0;
+            float best = -INFINITY;
+            int arg = 0x7FFFFFFF;
+            if (has) {
+                float mx = -INFINITY;
+                for (int j = lane; j < P; j += 64) mx = fmaxf(mx, S[j]);
+                mx = wave_max(mx);
+                float es = 0.0f;
+                for (int j = lane; j < P; j += 64) es += expf(S[j] - mx);
+                const float den = wave_sum(es);
+                for (int j = lane; j < P; j += 64) {
+                    const float p = expf(S[j] - mx) / den;
+                    if (prob) prob[q * P + j] = p;
+                    if (p > best) {
+                        best = p;
+                        arg = j;
+                    }
+                }
+            } else if (prob) {
+                for (int j = lane; j < P; j += 64) prob[q * P + j] = 0.0f;
+            }
+            wave_argmax(best, arg);
+            if (label && lane == 0) label[q] = (has && best >= pp.threshold) ? arg : -1;
+        }
+        __syncthreads();
     }
 }
 
@@ -4323,7 +4325,8 @@ hipError_t launch_predict(const MapDev &md, const PredictParams &pp, const float
         return hipGetLastError();
     }
     const bool fast = pp.L % 16 == 0 && ((uintptr_t)pp.protos & 15u) == 0;
-    const dim3 grid((unsigned)((m + 15) / 16)), block(256);
+    // (a launch holds fewer than 2^32 threads: beyond 2^22 points the workgroups stride)
+    const dim3 grid((unsigned)std::min<long long>((m + 15) / 16, 1 << 18)), block(256);
 #define SLIM_PREDICT(PMAX, FAST) \
     hipLaunchKernelGGL((k_predict_open<PMAX, FAST>), grid, block, 0, s, md, pp, xyz, m, prob, label, var)
     // the similarities sit in LDS: up to 128 prototypes five workgroups fit a CU
