@@ -4164,7 +4164,7 @@ __global__ __launch_bounds__(256) void k_predict(const MapDev md, const PredictP
 // Open set: a workgroup takes 16 points.  Their means against the prototypes
 // are a contraction (m x L by L x P), done on the matrix cores in binary32: each
 // of the four waves takes every fourth run of 16 components of all rows, 16 x 16
-// products at a time (v_mfma_f32_16x16x4f32), four tiles of 16 prototypes at a time.
+// products at a time (v_mfma_f32_16x16x4f32), CT tiles of 16 prototypes at a time.
 // A lane loads four consecutive components of one row (lane mod 16) for the four
 // steps of a run, so the fragments come straight from the records and from the
 // prototypes, which stay in L2: no staging.  Norms are formed from the same
@@ -4183,15 +4183,20 @@ __global__ __launch_bounds__(256) void k_predict(const MapDev md, const PredictP
 // prototypes x 512 components take 115 us; one wave a point, which forms every dot
 // product and every prototype norm by itself, 960 us.  With 32 points a workgroup,
 // half the prototype traffic but a third fewer waves, 180 us.
+// Where none of the 16 points has a record nothing is contracted (2,000 such points,
+// 1,024 prototypes of 512 components: 121 us if it is).
+// CT = 1 (at most 16 prototypes): no work for tiles that are not there, and four
+// runs' loads in flight.  2,000 points, 2 prototypes of 1,024 components: 20 -> 15 us
+// (one wave a point 14), 16,384 points 38 -> 25 us (49).
 // FAST: L a multiple of 16 and 16-byte aligned prototypes, no edge in a load.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <int PMAX, bool FAST>
+template <int PMAX, int CT, bool FAST>
 __global__ __launch_bounds__(256, PMAX == 1024 ? 1 : 5) void k_predict_open(const MapDev md, const PredictParams pp,
                                                                            const float *xyz, long long m, float *prob,
                                                                            int32_t *label, float *var)
 {
-    constexpr int TQ = 16, CT = 4, PC = 16 * CT;
+    constexpr int TQ = 16, PC = 16 * CT, U = 4 / CT;
     __shared__ float sims[TQ][PMAX];
     __shared__ float part[4][TQ][PC + 4];
     __shared__ float n2s[4][TQ], q2s[4][PC];
@@ -4202,7 +4207,9 @@ __global__ __launch_bounds__(256, PMAX == 1024 ? 1 : 5) void k_predict_open(cons
         const long long qc = q0 + c;
         const int rec = qc < m ? (int)lookup_point(md, pp.vs, xyz[3 * qc], xyz[3 * qc + 1], xyz[3 * qc + 2]) : -1;
         const float *A = md.vox + (size_t)(rec >= 0 ? rec : 0) * md.rec_stride + 2;
-        for (int p0 = 0; p0 < P; p0 += PC) {
+        // (every wave holds all 16 records: the branch is the workgroup's)
+        const int P1 = __ballot(rec >= 0) != 0ull ? P : 0;
+        for (int p0 = 0; p0 < P1; p0 += PC) {
             f32x4_t acc[CT];
             float n2 = 0.0f, q2[CT];
 #pragma unroll
@@ -4210,42 +4217,48 @@ __global__ __launch_bounds__(256, PMAX == 1024 ? 1 : 5) void k_predict_open(cons
                 q2[u] = 0.0f;
                 acc[u] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
             }
-            for (int s = w; 16 * s < L; s += 4) {
-                const int k = 16 * s + 4 * g;
-                float a[4], b[CT][4];
-                if constexpr (FAST) {
-                    const bool has = rec >= 0;
-                    const float2 x = has ? *(const float2 *)(A + k) : make_float2(0.0f, 0.0f);
-                    const float2 y = has ? *(const float2 *)(A + k + 2) : make_float2(0.0f, 0.0f);
-                    a[0] = x.x; a[1] = x.y; a[2] = y.x; a[3] = y.y;
-                } else {
+            for (int s = w; 16 * s < L; s += 4 * U) {
+                float a[U][4], b[U][CT][4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) a[j] = rec >= 0 && k + j < L ? A[k + j] : 0.0f;
-                }
-#pragma unroll
-                for (int u = 0; u < CT; ++u) {
-                    const int p = p0 + 16 * u + c;
-                    const float *B = pp.protos + (size_t)(p < P ? p : 0) * L + k;
+                for (int v = 0; v < U; ++v) {
+                    const int k = 16 * (s + 4 * v) + 4 * g;
                     if constexpr (FAST) {
-                        const float4 x = p < P ? *(const float4 *)B : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                        b[u][0] = x.x; b[u][1] = x.y; b[u][2] = x.z; b[u][3] = x.w;
+                        const bool has = rec >= 0 && k < L;
+                        const float2 x = has ? *(const float2 *)(A + k) : make_float2(0.0f, 0.0f);
+                        const float2 y = has ? *(const float2 *)(A + k + 2) : make_float2(0.0f, 0.0f);
+                        a[v][0] = x.x; a[v][1] = x.y; a[v][2] = y.x; a[v][3] = y.y;
                     } else {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) b[u][j] = p < P && k + j < L ? B[j] : 0.0f;
+                        for (int j = 0; j < 4; ++j) a[v][j] = rec >= 0 && k + j < L ? A[k + j] : 0.0f;
+                    }
+#pragma unroll
+                    for (int u = 0; u < CT; ++u) {
+                        const int p = p0 + 16 * u + c;
+                        const float *B = pp.protos + (size_t)(p < P ? p : 0) * L + k;
+                        if constexpr (FAST) {
+                            const float4 x = p < P && k < L ? *(const float4 *)B : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                            b[v][u][0] = x.x; b[v][u][1] = x.y; b[v][u][2] = x.z; b[v][u][3] = x.w;
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) b[v][u][j] = p < P && k + j < L ? B[j] : 0.0f;
+                        }
                     }
                 }
-                n2 += fmaf(a[3], a[3], fmaf(a[2], a[2], fmaf(a[1], a[1], a[0] * a[0])));
 #pragma unroll
-                for (int u = 0; u < CT; ++u) {
-                    const float *y = b[u];
-                    const f32x4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
-                    f32x4_t z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], y[0], zero, 0, 0, 0);
-                    f32x4_t z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], y[2], zero, 0, 0, 0);
-                    z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], y[1], z0, 0, 0, 0);
-                    z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], y[3], z1, 0, 0, 0);
-                    acc[u] += z0 + z1;
-                    __builtin_amdgcn_sched_barrier(0);
-                    q2[u] += fmaf(y[3], y[3], fmaf(y[2], y[2], fmaf(y[1], y[1], y[0] * y[0])));
+                for (int v = 0; v < U; ++v) {
+                    n2 += fmaf(a[v][3], a[v][3], fmaf(a[v][2], a[v][2], fmaf(a[v][1], a[v][1], a[v][0] * a[v][0])));
+#pragma unroll
+                    for (int u = 0; u < CT; ++u) {
+                        const float *y = b[v][u];
+                        const f32x4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                        f32x4_t z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v][0], y[0], zero, 0, 0, 0);
+                        f32x4_t z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v][2], y[2], zero, 0, 0, 0);
+                        z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v][1], y[1], z0, 0, 0, 0);
+                        z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v][3], y[3], z1, 0, 0, 0);
+                        acc[u] += z0 + z1;
+                        __builtin_amdgcn_sched_barrier(0);
+                        q2[u] += fmaf(y[3], y[3], fmaf(y[2], y[2], fmaf(y[1], y[1], y[0] * y[0])));
+                    }
                 }
             }
             n2 += __shfl_xor(n2, 16, 64);
@@ -4351,13 +4364,15 @@ hipError_t launch_predict(const MapDev &md, const PredictParams &pp, const float
     const bool fast = pp.L % 16 == 0 && ((uintptr_t)pp.protos & 15u) == 0;
     // (a launch holds fewer than 2^32 threads: beyond 2^22 points the workgroups stride)
     const dim3 grid((unsigned)std::min<long long>((m + 15) / 16, 1 << 18)), block(256);
-#define SLIM_PREDICT(PMAX, FAST) \
-    hipLaunchKernelGGL((k_predict_open<PMAX, FAST>), grid, block, 0, s, md, pp, xyz, m, prob, label, var)
+#define SLIM_PREDICT(PMAX, CT, FAST) \
+    hipLaunchKernelGGL((k_predict_open<PMAX, CT, FAST>), grid, block, 0, s, md, pp, xyz, m, prob, label, var)
     // the similarities sit in LDS: up to 128 prototypes five workgroups fit a CU
-    if (pp.P <= 128 && fast) SLIM_PREDICT(128, true);
-    else if (pp.P <= 128) SLIM_PREDICT(128, false);
-    else if (fast) SLIM_PREDICT(1024, true);
-    else SLIM_PREDICT(1024, false);
+    if (pp.P <= 16 && fast) SLIM_PREDICT(16, 1, true);
+    else if (pp.P <= 16) SLIM_PREDICT(16, 1, false);
+    else if (pp.P <= 128 && fast) SLIM_PREDICT(128, 4, true);
+    else if (pp.P <= 128) SLIM_PREDICT(128, 4, false);
+    else if (fast) SLIM_PREDICT(1024, 4, true);
+    else SLIM_PREDICT(1024, 4, false);
 #undef SLIM_PREDICT
     return hipGetLastError();
 }
