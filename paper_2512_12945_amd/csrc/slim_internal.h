@@ -143,7 +143,8 @@ struct LossParams {
     float alpha0;
     float *loss;             // 3 floats: total, cross-entropy term, L1 term
     float *adj;              // per record: K adjoints dL/dc, then dL/dD (stride adj_stride)
-    int32_t *adj_cnt;        // per record: surface samples in the voxel, and whether it has a row of adjoints
+    int32_t *adj_cnt;        // per record: surface samples in the voxel
+    uchar2 *adj_flag;        // per record: whether dL/dD and dL/dc have been written
     int adj_stride;
     float *part;             // block partial sums
     int32_t *part_cnt;       // block partial sample counts

@@ -121,7 +121,7 @@ struct slim_map {
     hipError_t noalloc_err = hipSuccess;  // outcome of the scratch address setup at create
     // loss adjoints (allocated by the first slim_map_loss)
     float *adj = nullptr;
-    int32_t *adj_cnt = nullptr;
+    int32_t *adj_cnt = nullptr;  // and the records' flags behind it
     float *part = nullptr;
     int32_t *part_cnt = nullptr;
     size_t part_cap = 0;
@@ -966,7 +966,7 @@ slim_status slim_map_loss(slim_map *m, const int32_t *keys, const int32_t *label
     slim_status r;
     if (!m->adj) {
         HIP_OK(hipStreamSynchronize(s));
-        if ((r = dalloc(m, &m->adj, nrec * astride)) || (r = dalloc(m, &m->adj_cnt, nrec))) return r;
+        if ((r = dalloc(m, &m->adj, nrec * astride)) || (r = dalloc(m, &m->adj_cnt, nrec + nrec / 2))) return r;
     }
     const size_t nparts = (size_t)((ns + kLossThreads - 1) / kLossThreads + (mv + kLossThreads - 1) / kLossThreads);
     if (nparts > m->part_cap) {
@@ -992,6 +992,7 @@ slim_status slim_map_loss(slim_map *m, const int32_t *keys, const int32_t *label
     lp.loss = loss;
     lp.adj = m->adj;
     lp.adj_cnt = m->adj_cnt;
+    lp.adj_flag = (uchar2 *)(m->adj_cnt + nrec);
     lp.adj_stride = astride;
     lp.part = m->part;
     lp.part_cnt = m->part_cnt;
@@ -1016,9 +1017,11 @@ slim_status slim_backward_rays(slim_map *m, const float *ranges, const float *di
     slim_status r = make_frame(m, nullptr, ranges, dirs, n, pose, logits, SLIM_IN_LOGIT_F32, &fp);
     if (r) return r;
     DeviceGuard g(m->cfg.device);
+    const size_t nrec = (size_t)m->md.max_pages * kPageVoxels;
     LossParams lp = {};
     lp.adj = m->adj;
     lp.adj_cnt = m->adj_cnt;
+    lp.adj_flag = (uchar2 *)(m->adj_cnt + nrec);
     lp.adj_stride = (m->cfg.num_classes + 1 + 3) & ~3;
     HIP_OK(launch_backward(fp, m->md, lp, grad_scale, grad_logits, grad_ranges, (hipStream_t)stream));
     return SLIM_OK;

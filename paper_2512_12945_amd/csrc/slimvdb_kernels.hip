@@ -3356,18 +3356,19 @@ __device__ __forceinline__ float block_sum(float v, float *red)
     return r;
 }
 
-// A record's word of adj_cnt: the surface samples in its voxel, and kAdjRow once
-// its row of adjoints has been written.  Only these words are cleared (4 bytes a
-// record instead of a row): a voxel that the loss does not list has no row and
-// carries zero adjoints into the backward.
-constexpr int kAdjRow = 1 << 30;
-
+// A record's bytes of adj_flag: nonzero once its dL/dD (x) and its dL/dc (y) have been
+// written.  Only these and the sample counts are cleared (6 bytes a record instead of
+// a row): what has not been written carries zero adjoints into the backward.  Two bytes,
+// each only ever set: a voxel listed twice, once without a class, keeps its dL/dc
+// whichever comes first.
 __global__ __launch_bounds__(256) void k_loss_clear(MapDev md, LossParams lp)
 {
     // (records come in pages of 64)
-    const size_t n = (size_t)md.st->pages_used * (kPageVoxels / 4), stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += stride)
-        ((int4 *)lp.adj_cnt)[i] = make_int4(0, 0, 0, 0);
+    const size_t pages = (size_t)md.st->pages_used, stride = (size_t)gridDim.x * blockDim.x;
+    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    const int4 zero = make_int4(0, 0, 0, 0);
+    for (size_t i = t; i < pages * (kPageVoxels / 4); i += stride) ((int4 *)lp.adj_cnt)[i] = zero;
+    for (size_t i = t; i < pages * (kPageVoxels / 8); i += stride) ((int4 *)lp.adj_flag)[i] = zero;
 }
 
 // Surface samples: per voxel count (integer, so order-free) and block partials
@@ -3440,21 +3441,25 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_voxels(FrameParams fp, Ma
             }
         }
         const float ay = lp.alpha0 + cy;
-        const float g = term ? inv_m / tot : 0.0f, gy = g - inv_m / ay;
-        if (term) ce = -logf(ay / tot);
         const float sg = D > 0.0f ? 1.0f : (D < 0.0f ? -1.0f : 0.0f);
-        const int cnt = lp.adj_cnt[rec] & (kAdjRow - 1);
-        const float ad = sg * (float)cnt * inv_mp;
-        for (int v = 0; v < lp.adj_stride / 4; ++v) {
-            float x[4];
+        const float ad = sg * (float)lp.adj_cnt[rec] * inv_mp;
+        if (term) {
+            const float g = inv_m / tot, gy = g - inv_m / ay;
+            ce = -logf(ay / tot);
+            for (int v = 0; v < lp.adj_stride / 4; ++v) {
+                float x[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int k = 4 * v + e;
-                x[e] = k < K ? (term && k == y ? gy : g) : (k == K ? ad : 0.0f);
+                for (int e = 0; e < 4; ++e) {
+                    const int k = 4 * v + e;
+                    x[e] = k < K ? (k == y ? gy : g) : (k == K ? ad : 0.0f);
+                }
+                A[v] = make_float4(x[0], x[1], x[2], x[3]);
             }
-            A[v] = make_float4(x[0], x[1], x[2], x[3]);
+            lp.adj_flag[rec].y = 1;
+        } else {
+            ((float *)A)[K] = ad;
         }
-        lp.adj_cnt[rec] = cnt | kAdjRow;
+        lp.adj_flag[rec].x = 1;
     }
     ce = block_sum(ce, red);
     if (threadIdx.x == 0) lp.part[nsb + blockIdx.x] = ce;
@@ -3581,12 +3586,13 @@ __global__ __launch_bounds__(4 * kBackRays) void k_backward_rays(FrameParams fp,
     constexpr int U = 4;
     for (int j0 = 0; j0 < ncell; j0 += U) {
         float4 a[U][NVL];
-        int rec[U], cnt[U];
+        int rec[U];
+        uchar2 flag[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             rec[u] = j0 + u < ncell ? s_cell[ray][j0 + u] : -1;
             const size_t r = (size_t)(rec[u] >= 0 ? rec[u] : 0);
-            cnt[u] = lp.adj_cnt[r];
+            flag[u] = lp.adj_flag[r];
 #pragma unroll
             for (int v = 0; v < NVL; ++v) {
                 const int q = sub + 4 * v;
@@ -3595,16 +3601,16 @@ __global__ __launch_bounds__(4 * kBackRays) void k_backward_rays(FrameParams fp,
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            // a voxel without a row (unlisted, or an unobserved record of an
-            // observed slab) has zero adjoints
-            if (rec[u] < 0 || !(cnt[u] & kAdjRow)) continue;
+            // a voxel that is not listed (or an unobserved record of an observed slab)
+            // has zero adjoints, one without a class zero dL/dc
+            if (rec[u] < 0 || !flag[u].x) continue;
 #pragma unroll
             for (int v = 0; v < NVL; ++v) {
                 const float x[4] = {a[u][v].x, a[u][v].y, a[u][v].z, a[u][v].w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int k = 4 * (sub + 4 * v) + e;
-                    if (k < K) G[v][e] += x[e];
+                    if (k < K && flag[u].y) G[v][e] += x[e];
                     if (k == K && ((inner >> (j0 + u)) & 1ull) && x[e] != 0.0f)
                         gr += x[e] / md.vox[(size_t)rec[u] * md.rec_stride + 1];
                 }
