@@ -82,6 +82,7 @@ struct DevState {
     unsigned long long leaves_used;
     unsigned long long pages_used;
     unsigned long long voxels_used;  // voxels with W > 0
+    unsigned long long filtered;     // leaves whose bits the render's filters have
     int status;       // first asynchronous error not yet reported
     int pass_failed;  // 0, or 1 + the first frame of a multi-frame pass that could not be applied
     // last frame (written by the commit)

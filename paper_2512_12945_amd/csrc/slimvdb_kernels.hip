@@ -4391,9 +4391,10 @@ hipError_t launch_predict(const MapDev &md, const PredictParams &pp, const float
 // Filters of the render: a bit per leaf, and per block of 8 x 8 x 8 leaves, taken
 // at their coordinates modulo 64 leaves and 32 blocks, set for every leaf of the
 // map, so that a clear bit means that nothing is there.  A ray through empty space
-// then reads LDS instead of the leaf table.  Every render sets the bits of all
-// leaves; none is cleared before the map is (leaves leave a map only then), so
-// renders of one map on several streams find theirs set.  (x, y, z: voxel keys.)
+// then reads LDS instead of the leaf table.  A render sets the bits of the leaves
+// beyond DevState::filtered, which the render kernel moves on once they are set; none
+// is cleared before the map is (leaves leave a map only then), so renders of one map
+// on several streams find theirs set.  (x, y, z: voxel keys.)
 __device__ __forceinline__ uint32_t leaf_bit(int x, int y, int z)
 {
     return (((uint32_t)x >> 3) & 63u) | ((((uint32_t)y >> 3) & 63u) << 6) | ((((uint32_t)z >> 3) & 63u) << 12);
@@ -4407,12 +4408,14 @@ __device__ __forceinline__ uint32_t block_bit(int x, int y, int z)
 static_assert(kFilterLog2 == 18 && kFilterBlockLog2 == 15, "6 bits of each leaf coordinate, 5 of each block's");
 
 // Bound by the atomics on one word: the leaves of a surface share few blocks, and
-// those a workgroup holds are gathered in LDS first (8,200 leaves: 24 -> 7 us).
+// those a workgroup holds are gathered in LDS first (8,200 new leaves: 24 -> 7 us).
+// (With the bits of all leaves set by every render, one of a single cell took 37 us
+// over 630,000 leaves; without the filters of any kind it takes 12.)
 __global__ __launch_bounds__(256) void k_render_filter(const MapDev md)
 {
     __shared__ uint32_t s_block[(1 << kFilterBlockLog2) / 32];
     const unsigned long long n = md.st->leaves_used;
-    const unsigned long long first = blockIdx.x * (unsigned long long)blockDim.x;
+    const unsigned long long first = md.st->filtered + blockIdx.x * (unsigned long long)blockDim.x;
     if (first >= n) return;
     constexpr int kWords = (1 << kFilterBlockLog2) / 32, kBase = (1 << kFilterLog2) / 32;
     for (int w = threadIdx.x; w < kWords; w += 256) s_block[w] = 0u;
@@ -4465,13 +4468,17 @@ __device__ __forceinline__ void render_step(float &tx, float &ty, float &tz, uin
 // many rays are at a binade's end somewhere in the wave.)
 constexpr int kRenderThreads = 256, kRenderCells = 8;
 
+template <bool FILTER>
 __global__ __launch_bounds__(kRenderThreads) void k_render(const MapDev md, const RenderParams rp,
                                                            float *depth, int32_t *key, int32_t *label)
 {
-    __shared__ uint32_t s_filter[kFilterWords];
-    for (int i = threadIdx.x; i < kFilterWords / 4; i += kRenderThreads)
-        ((uint4 *)s_filter)[i] = ((const uint4 *)md.filter)[i];
-    __syncthreads();
+    __shared__ uint32_t s_filter[FILTER ? kFilterWords : 4];
+    if constexpr (FILTER) {
+        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) md.st->filtered = md.st->leaves_used;
+        for (int i = threadIdx.x; i < kFilterWords / 4; i += kRenderThreads)
+            ((uint4 *)s_filter)[i] = ((const uint4 *)md.filter)[i];
+        __syncthreads();
+    }
     // 4 waves of 8 x 8 pixels
     const int lane = lane_id(), wv = threadIdx.x >> 6;
     const int px = blockIdx.x * 32 + wv * 8 + (lane & 7), py = blockIdx.y * 8 + (lane >> 3);
@@ -4531,14 +4538,17 @@ __global__ __launch_bounds__(kRenderThreads) void k_render(const MapDev md, cons
             // (past the key range no cell is observed, and a ray does not come back)
             if (((uint32_t)(k[0] + kKeyLimit) | (uint32_t)(k[1] + kKeyLimit) | (uint32_t)(k[2] + kKeyLimit)) >= 2u * kKeyLimit)
                 break;
-            const uint32_t bb = block_bit(k[0], k[1], k[2]), lb = leaf_bit(k[0], k[1], k[2]);
-            const uint32_t bw = s_filter[bb >> 5], lw = s_filter[lb >> 5];
-            uint32_t bits = kBlockBits;
-            int slot = -1;
-            if ((bw >> (bb & 31)) & 1u) {
-                bits = kLeafBits;
-                if ((lw >> (lb & 31)) & 1u) slot = map_find(md, pack_leaf(k[0] >> 3, k[1] >> 3, k[2] >> 3));
+            uint32_t bits = kLeafBits;
+            bool look = true;
+            if constexpr (FILTER) {
+                const uint32_t bb = block_bit(k[0], k[1], k[2]), lb = leaf_bit(k[0], k[1], k[2]);
+                const uint32_t bw = s_filter[bb >> 5], lw = s_filter[lb >> 5];
+                const bool block = (bw >> (bb & 31)) & 1u;
+                bits = block ? kLeafBits : kBlockBits;
+                look = block && ((lw >> (lb & 31)) & 1u);
             }
+            int slot = -1;
+            if (look) slot = map_find(md, pack_leaf(k[0] >> 3, k[1] >> 3, k[2] >> 3));
             const int l[3] = {k[0] >> 3, k[1] >> 3, k[2] >> 3};
             at = kBias + (((uint32_t)k[0] & 63u) << 16) + (((uint32_t)k[1] & 63u) << 8) + ((uint32_t)k[2] & 63u);
             const uint32_t at0 = at, home = at & bits;
@@ -4647,13 +4657,24 @@ __global__ __launch_bounds__(kRenderThreads) void k_render(const MapDev md, cons
     if (label) label[i] = out_l;
 }
 
+// Rays of at most this many cells are walked without the filters (every leaf on the
+// way is looked up): the filters' launch and their copy to LDS take 3 to 7 us, more
+// than a short walk saves.  Images of 64x48 over 63,000 scattered leaves, without and
+// with: 1 cell 11 and 19 us, 32 cells 15 and 19, 48 cells 22 and 19, 100 cells 44 and
+// 33; over the 8,200 leaves of a street 11 and 16, 30 and 33, 50 and 54, 95 and 99.
+constexpr float kNearCells = 48.0f;
+
 hipError_t launch_render(const MapDev &md, const RenderParams &rp, float *depth, int32_t *key, int32_t *label,
                          hipStream_t s)
 {
     if (rp.width <= 0 || rp.height <= 0) return hipGetLastError();
-    hipLaunchKernelGGL(k_render_filter, dim3(256), dim3(256), 0, s, md);
     const dim3 grid((rp.width + 31) / 32, (rp.height + 7) / 8);
-    hipLaunchKernelGGL(k_render, grid, dim3(kRenderThreads), 0, s, md, rp, depth, key, label);
+    if (rp.t1 - rp.t0 <= kNearCells * rp.vs) {
+        hipLaunchKernelGGL(k_render<false>, grid, dim3(kRenderThreads), 0, s, md, rp, depth, key, label);
+    } else {
+        hipLaunchKernelGGL(k_render_filter, dim3(256), dim3(256), 0, s, md);
+        hipLaunchKernelGGL(k_render<true>, grid, dim3(kRenderThreads), 0, s, md, rp, depth, key, label);
+    }
     return hipGetLastError();
 }
 
