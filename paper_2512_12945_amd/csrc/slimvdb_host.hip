@@ -1165,7 +1165,8 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
         std::vector<int> all(nmaps);
         for (int i = 0; i < nmaps; ++i) all[i] = i;
         plan.plan_blocks = std::max(shape.plan_blocks, nmaps);
-        plan.bucket_blocks = std::max(shape.bucket_blocks, nmaps);
+        // (a workgroup emits whole walk blocks)
+        plan.bucket_blocks = std::max(std::min(shape.bucket_blocks, plan.walk_blocks), nmaps);
         share(all.data(), nmaps, plan.plan_blocks, plan_first);
         share(all.data(), nmaps, plan.bucket_blocks, bucket_first);
         for (int g = 0; g < plan.ngroups; ++g) {
