@@ -1121,7 +1121,9 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
             const int wb = start[i + 1] - start[i];
             c[0] = (uint32_t)((wb + shape.walk_chunk - 1) / shape.walk_chunk);
             c[1] = share(shape.plan_blocks, i, 0xFFFFu);
-            c[2] = share(shape.bucket_blocks, i, 0xFFFFu);
+            // (an item emits whole walk blocks: with 4,096 items for 1,600 blocks most did
+            // nothing but wait for their turn, 16 maps 5,340 us, now 4,720)
+            c[2] = share(shape.bucket_blocks, i, std::min(0xFFFFu, (uint32_t)wb));
             c[3] = share(shape.leaf_blocks, i, leaf_cap);
             c[4] = voxel_combine_arg(kinds[i]) != -2 ? share(shape.leaf_blocks, i, 0xFFFFu) : 0u;
             c[5] = 1;
