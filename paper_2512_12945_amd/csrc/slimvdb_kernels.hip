@@ -1119,7 +1119,7 @@ __device__ __forceinline__ void combine_lane(const FrameParams &fp, const MapDev
     for (int k = 0; k < KMAX; ++k) acc[k] = 0.0f;
     // one row per lane at a time, added in point order: four workgroups per CU hide
     // more than two rows and three workgroups do (131,071 rays, 20 classes: 56 and
-    // 65 us; four rows spill)
+    // 65 us)
     for (uint32_t q = 0; q < n; ++q) {
         const float *row = rows + (size_t)(keys[q] & kPidMask) * stride;
         float x[KMAX];
@@ -2207,6 +2207,13 @@ __device__ __forceinline__ void leaf_fuse_range(const FrameParams &fp, const Map
     __syncthreads();
 }
 
+// Row kernels at four workgroups per CU hold 128 registers and spill a few (4, 11 and
+// 18 with 16, 24 and 32 classes in registers; none with 8).  With three, which do not,
+// a frame of probability rows with 5, 12, 20 and 28 classes takes 48.5, 49.3, 51.2 and
+// 52.8 us at 4,096 rays (with four 48.0, 49.7, 52.0 and 54.3), 62.7, 71.6, 76.2 and
+// 81.8 us at 65,536 (63.3, 65.9, 71.2 and 78.1), 97, 112, 119 and 127 us at 131,071
+// (98, 102, 110 and 118); with voxels twice as large, 20 classes, 66,000 rays 115 us
+// (121).
 template <int KMAX, bool WAVE, bool ROWS>
 __global__ __launch_bounds__(kLeafThreads, WAVE ? 1 : 4) void k_leaf_fuse(FrameParams fp, MapDev md)
 {
@@ -2215,9 +2222,12 @@ __global__ __launch_bounds__(kLeafThreads, WAVE ? 1 : 4) void k_leaf_fuse(FrameP
 }
 
 // The maps mb.subset[0 .. nsubset) of a batch, all of this kernel's kind, each
-// on its share of the grid.
+// on its share of the grid.  Row kernels at four workgroups per CU up to 24 classes (16
+// maps of 30,000 rays with 5, 12 and 20 classes 347, 387 and 464 us; at three 386, 417
+// and 477), at three above (28 classes: at four 56 registers spill, 546 us, at three
+// none, 501).
 template <int KMAX, bool WAVE, bool ROWS>
-__global__ __launch_bounds__(kLeafThreads, WAVE ? 1 : 4) void k_leaf_fuse_batch(MapBatch mb)
+__global__ __launch_bounds__(kLeafThreads, WAVE ? 1 : (KMAX > 24 ? 3 : 4)) void k_leaf_fuse_batch(MapBatch mb)
 {
     __shared__ LeafShared sh;
     const int q = batch_map(mb.part_first, mb.nsubset, blockIdx.x), i = mb.subset[q];
