@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "slim_internal.h"
@@ -90,6 +91,7 @@ struct slim_map {
     MapDev md = {};
     size_t hcap = 0;
     size_t pair_cap = 0;
+    char *pair_block[2] = {nullptr, nullptr};  // the pair buffers of either staging buffer
     // second staging buffer and walk stream of slim_integrate_sequence: the
     // walk of frame t + 1 runs beside the rest of frame t
     MapDev md1 = {};
@@ -100,6 +102,7 @@ struct slim_map {
     bool used[2] = {false, false};
     // extraction scratch
     ExtractScratch ext = {};
+    char *ext_block = nullptr;
     // pinned copy of the counters for the calls that read them back, one at a time
     DevState *host_st = nullptr;
     std::mutex host_lock;
@@ -141,6 +144,48 @@ slim_status dalloc(slim_map *m, T **p, size_t count)
     m->allocs.push_back(q);
     *p = (T *)q;
     return SLIM_OK;
+}
+
+// Several arrays in one allocation, at 256-byte boundaries: place(piece) names each
+// as piece(pointer, count).  (An allocation costs the call that makes it 30 to 100 us.)
+template <class F>
+slim_status dalloc_block(slim_map *m, char **block, F place)
+{
+    auto carve = [&](char *base) {
+        size_t at = 0;
+        place([&](auto *&p, size_t count) {
+            p = base ? (std::remove_reference_t<decltype(p)>)(base + at) : nullptr;
+            at += (std::max<size_t>(count, 1) * sizeof(*p) + 255) & ~size_t(255);
+        });
+        return at;
+    };
+    *block = nullptr;
+    const slim_status r = dalloc(m, block, carve(nullptr));
+    if (!r) carve(*block);
+    return r;
+}
+
+// What a staging buffer owns besides its pair buffers, for a table of cap slots.
+template <class P>
+void place_staging(MapDev &md, size_t cap, P piece)
+{
+    piece(md.skeys, cap);
+    piece(md.touched, cap);
+    piece(md.touched_key, cap);
+    piece(md.pos_count, cap);
+    piece(md.pos_slab, cap);
+    piece(md.pos_plan, cap);
+    piece(md.pos_pages, 2 * cap);
+    piece(md.items, cap);
+    piece(md.items_small, cap);
+    piece(md.fs, 1);
+}
+
+void dfree(slim_map *m, void *p)
+{
+    if (!p) return;
+    (void)hipFree(p);
+    m->allocs.erase(std::remove(m->allocs.begin(), m->allocs.end(), p), m->allocs.end());
 }
 
 void free_batch(slim_map *m)
@@ -216,40 +261,30 @@ slim_status ensure_pairs(slim_map *m, size_t need, hipStream_t s, int buf = 0)
     size_t cap = std::max<size_t>(need, pcap + pcap / 2);
     cap = std::min<size_t>(cap, 0xFFFFFFF0ull);
     MapDev &md = buf ? m->md1 : m->md;
-    void *ptrs[11] = {md.ray_bits, md.ray_run, md.pair_key, md.pair_tsdf, md.srt_kv,  md.srt_lab,
-                      md.tmp_key, md.tmp_tsdf, md.work,      md.vox_list, md.items_big};
-    for (void *p : ptrs) {
-        if (!p) continue;
-        (void)hipFree(p);
-        m->allocs.erase(std::remove(m->allocs.begin(), m->allocs.end(), p), m->allocs.end());
-    }
-    md.ray_bits = nullptr;
-    md.ray_run = nullptr;
+    char *&block = m->pair_block[buf];
+    dfree(m, block);
+    pcap = 0;
     md.ray_cap = 0;
-    md.pair_key = md.tmp_key = nullptr;
-    md.pair_tsdf = md.tmp_tsdf = nullptr;
-    md.srt_kv = nullptr;
-    md.srt_lab = nullptr;
-    md.work = nullptr;
-    md.vox_list = nullptr;
-    md.items_big = nullptr;
+    md.pair_cap = 0;
+    md.work_cap = 0;
     // a large leaf has more than kLeafLdsPairs pairs and at most 8 slab items
     const size_t wcap = cap / (kLeafLdsPairs / kLeafPages) + kLeafPages;
-    slim_status r;
     // rays of `need` pairs, and a partial workgroup of each frame of a pass
     const size_t rays = cap / (size_t)m->maxsteps + (size_t)kWalkThreads * (kPassFrames + 1);
-    if ((r = dalloc(m, &md.ray_bits, 3 * rays)) || (r = dalloc(m, &md.ray_run, (size_t)kMaxRuns * rays)) ||
-        (r = dalloc(m, &md.pair_key, cap)) || (r = dalloc(m, &md.pair_tsdf, cap)) ||
-        (r = dalloc(m, &md.srt_kv, cap)) ||
-        (r = dalloc(m, &md.srt_lab, cap)) || (r = dalloc(m, &md.tmp_key, cap)) ||
-        (r = dalloc(m, &md.tmp_tsdf, cap)) ||
-        (r = dalloc(m, &md.work, wcap)) || (r = dalloc(m, &md.vox_list, cap)) ||
-        (r = dalloc(m, &md.items_big, wcap))) {
-        pcap = 0;
-        md.pair_cap = 0;
-        md.work_cap = 0;
-        return r;
-    }
+    const slim_status r = dalloc_block(m, &block, [&](auto piece) {
+        piece(md.ray_bits, 3 * rays);
+        piece(md.ray_run, (size_t)kMaxRuns * rays);
+        piece(md.pair_key, cap);
+        piece(md.pair_tsdf, cap);
+        piece(md.srt_kv, cap);
+        piece(md.srt_lab, cap);
+        piece(md.tmp_key, cap);
+        piece(md.tmp_tsdf, cap);
+        piece(md.work, wcap);
+        piece(md.vox_list, cap);
+        piece(md.items_big, wcap);
+    });
+    if (r) return r;
     pcap = cap;
     md.ray_cap = rays;
     md.pair_cap = (uint32_t)cap;
@@ -330,16 +365,17 @@ slim_status slim_map_create(const slim_map_config *config, slim_map **out)
     md.wave_pairs = 0;
     md.slab_pairs = 0;
     const size_t L = (size_t)config->max_leaves, NP = (size_t)md.max_pages;
-    if ((r = dalloc(m, &md.htab, cap)) || (r = dalloc(m, &md.skeys, cap)) ||
-        (r = dalloc(m, &md.touched, cap)) || (r = dalloc(m, &md.touched_key, cap)) ||
-        (r = dalloc(m, &md.pos_count, cap)) ||
-        (r = dalloc(m, &md.pos_slab, cap)) || (r = dalloc(m, &md.pos_plan, cap)) ||
-        (r = dalloc(m, &md.pos_pages, 2 * cap)) || (r = dalloc(m, &md.items, cap)) ||
-        (r = dalloc(m, &md.items_small, cap)) || (r = dalloc(m, &md.leaf_key, L)) ||
-        (r = dalloc(m, &md.leaf_page, L * kLeafPages)) || (r = dalloc(m, &md.leaf_occ, L * kMaskWords)) ||
-        (r = dalloc(m, &md.vox, NP * kPageVoxels * (size_t)md.rec_stride)) ||
-        (r = dalloc(m, &md.st, 1)) ||
-        (r = dalloc(m, &md.fs, 1)) || (r = dalloc(m, &md.filter, kFilterWords))) {
+    char *block;
+    r = dalloc_block(m, &block, [&](auto piece) {
+        place_staging(md, cap, piece);
+        piece(md.htab, cap);
+        piece(md.leaf_key, L);
+        piece(md.leaf_page, L * kLeafPages);
+        piece(md.leaf_occ, L * kMaskWords);
+        piece(md.st, 1);
+        piece(md.filter, kFilterWords);
+    });
+    if (r || (r = dalloc(m, &md.vox, NP * kPageVoxels * (size_t)md.rec_stride))) {
         free_all(m);
         delete m;
         return r;
@@ -496,12 +532,6 @@ slim_status ensure_buffer1(slim_map *m, hipStream_t s)
 {
     if (m->have1) return SLIM_OK;
     MapDev md = m->md;
-    md.skeys = nullptr;
-    md.touched = md.pos_count = md.pos_slab = nullptr;
-    md.touched_key = nullptr;
-    md.pos_plan = md.pos_pages = nullptr;
-    md.items = md.items_small = nullptr;
-    md.fs = nullptr;
     md.ray_bits = nullptr;
     md.ray_run = nullptr;
     md.ray_cap = 0;
@@ -516,12 +546,8 @@ slim_status ensure_buffer1(slim_map *m, hipStream_t s)
     md.work_cap = 0;
     const size_t cap = m->hcap;
     slim_status r;
-    if ((r = dalloc(m, &md.skeys, cap)) || (r = dalloc(m, &md.touched, cap)) ||
-        (r = dalloc(m, &md.touched_key, cap)) || (r = dalloc(m, &md.pos_count, cap)) ||
-        (r = dalloc(m, &md.pos_slab, cap)) || (r = dalloc(m, &md.pos_plan, cap)) ||
-        (r = dalloc(m, &md.pos_pages, 2 * cap)) || (r = dalloc(m, &md.items, cap)) ||
-        (r = dalloc(m, &md.items_small, cap)) || (r = dalloc(m, &md.fs, 1)))
-        return r;
+    char *block;
+    if ((r = dalloc_block(m, &block, [&](auto piece) { place_staging(md, cap, piece); }))) return r;
     HIP_OK(hipStreamCreateWithFlags(&m->wstream, hipStreamNonBlocking));
     // these events only order work between the map's two streams on the GPU:
     // device-scope release, no system-scope cache writeback at each record
@@ -803,15 +829,15 @@ slim_status slim_extract(slim_map *m, int64_t capacity, int32_t *keys, float *d,
     hipStream_t s = (hipStream_t)stream;
     if ((size_t)st.leaves > m->ext_cap) {
         HIP_OK(hipStreamSynchronize(s));
-        for (void *p : {(void *)m->ext.keys, (void *)m->ext.keys2}) {
-            if (!p) continue;
-            (void)hipFree(p);
-            m->allocs.erase(std::remove(m->allocs.begin(), m->allocs.end(), p), m->allocs.end());
-        }
+        dfree(m, m->ext_block);
         m->ext = {};
         m->ext_cap = 0;
         const size_t cap = (size_t)st.leaves;
-        if ((r = dalloc(m, &m->ext.keys, cap)) || (r = dalloc(m, &m->ext.keys2, cap))) return r;
+        r = dalloc_block(m, &m->ext_block, [&](auto piece) {
+            piece(m->ext.keys, cap);
+            piece(m->ext.keys2, cap);
+        });
+        if (r) return r;
         m->ext_cap = cap;
     }
     HIP_OK(launch_extract(m->md, m->nsem, st.leaves, m->ext, keys, d, w, m->nsem ? sem : nullptr, s));
@@ -971,11 +997,8 @@ slim_status slim_map_loss(slim_map *m, const int32_t *keys, const int32_t *label
     const size_t nparts = (size_t)((ns + kLossThreads - 1) / kLossThreads + (mv + kLossThreads - 1) / kLossThreads);
     if (nparts > m->part_cap) {
         HIP_OK(hipStreamSynchronize(s));
-        for (void *p : {(void *)m->part, (void *)m->part_cnt}) {
-            if (!p) continue;
-            (void)hipFree(p);
-            m->allocs.erase(std::remove(m->allocs.begin(), m->allocs.end(), p), m->allocs.end());
-        }
+        dfree(m, m->part);
+        dfree(m, m->part_cnt);
         m->part = nullptr;
         m->part_cnt = nullptr;
         m->part_cap = 0;
