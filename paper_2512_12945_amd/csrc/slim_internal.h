@@ -25,6 +25,11 @@ constexpr int kLeafPages = kLeafVoxels / kPageVoxels;
 constexpr int kWalkThreads = SLIM_WALK_THREADS;  // rays per walk block
 constexpr int kWalkTable = 8 * kWalkThreads;     // block-local leaf table: at most 8 leaf runs per ray
 constexpr int kMaxRuns = 8;                  // leaves a ray visits: sdf_trunc <= 6 voxel_size keeps it within 7
+// cells of a ray: 3 ceil(2 sdf_trunc / voxel_size) + 4, where sdf_trunc <= 6 voxel_size in
+// binary32 can round the quotient past 12
+constexpr int kMaxCells = 3 * 13 + 4;
+constexpr int kVisitShift = 56;              // ray record: kept cells in the low bits, the last visit's index above
+static_assert(kMaxCells <= kVisitShift, "a ray's cells fit the record's bits");
 constexpr int kLeafThreads = 256;
 constexpr int kLeafBatch = 8;                // loads in flight per thread in the leaf kernel
 constexpr int kLeafLdsPairs = kLeafBatch * kLeafThreads;  // pairs a leaf holds in LDS at once
@@ -219,7 +224,6 @@ struct MapDev {
                           // starts at the bucket of each large leaf
     uint32_t *tmp_key;    // scratch of large leaves: pairs binned by voxel offset
     float *tmp_tsdf;
-    uint32_t pair_cap;
     int2 *work;           // work items (index in items_big, slab or range) of large leaves
     uint32_t work_cap;
     uint4 *vox_list;      // wave-combine voxels: (record, pairs | existed << 31, first sorted pair, 0)

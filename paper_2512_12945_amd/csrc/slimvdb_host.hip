@@ -265,7 +265,6 @@ slim_status ensure_pairs(slim_map *m, size_t need, hipStream_t s, int buf = 0)
     dfree(m, block);
     pcap = 0;
     md.ray_cap = 0;
-    md.pair_cap = 0;
     md.work_cap = 0;
     // a large leaf has more than kLeafLdsPairs pairs and at most 8 slab items
     const size_t wcap = cap / (kLeafLdsPairs / kLeafPages) + kLeafPages;
@@ -287,7 +286,6 @@ slim_status ensure_pairs(slim_map *m, size_t need, hipStream_t s, int buf = 0)
     if (r) return r;
     pcap = cap;
     md.ray_cap = rays;
-    md.pair_cap = (uint32_t)cap;
     md.work_cap = (uint32_t)wcap;
     return SLIM_OK;
 }
@@ -345,7 +343,7 @@ slim_status slim_map_create(const slim_map_config *config, slim_map **out)
               : config->sem_mode == SLIM_SEM_OPEN_LAST   ? config->embed_dim
                                                          : 0;
     m->maxsteps = max_steps(config->voxel_size, config->sdf_trunc);
-    if (m->maxsteps > 64) {  // the walk kernel records a ray's cells in 64-bit masks
+    if (m->maxsteps > kMaxCells) {  // what the walk's records and the backward hold
         delete m;
         return fail(SLIM_ERR_UNSUPPORTED, "sdf_trunc / voxel_size too large");
     }
@@ -542,7 +540,6 @@ slim_status ensure_buffer1(slim_map *m, hipStream_t s)
     md.work = nullptr;
     md.vox_list = nullptr;
     md.items_big = nullptr;
-    md.pair_cap = 0;
     md.work_cap = 0;
     const size_t cap = m->hcap;
     slim_status r;
@@ -1133,7 +1130,6 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
     if (shape.persistent) {
         std::vector<uint32_t> cnt((size_t)nmaps * kPersistStages, 0u);
         const long long wtot = start[nmaps];
-        const uint32_t leaf_cap = (uint32_t)m0->cus * kMaxLeafBlocksPerCu;
         auto share = [&](int total, int i, uint32_t cap) {
             const long long wb = start[i + 1] - start[i];
             const long long c = ((long long)total * wb + wtot - 1) / wtot;
@@ -1147,7 +1143,7 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
             // (an item emits whole walk blocks: with 4,096 items for 1,600 blocks most did
             // nothing but wait for their turn, 16 maps 5,340 us, now 4,720)
             c[2] = share(shape.bucket_blocks, i, std::min(0xFFFFu, (uint32_t)wb));
-            c[3] = share(shape.leaf_blocks, i, leaf_cap);
+            c[3] = share(shape.leaf_blocks, i, 0xFFFFu);
             c[4] = voxel_combine_arg(kinds[i]) != -2 ? share(shape.leaf_blocks, i, 0xFFFFu) : 0u;
             c[5] = 1;
         }

@@ -365,8 +365,6 @@ struct WalkShared {
 // buckets are laid out: which cells it kept and how it steps (bits), and for each
 // leaf it visits the staging position and the first of its ranks in the leaf's
 // bucket.
-constexpr int kVisitShift = 56;  // kept cells in the low bits (at most 43), the last visit's index above
-
 __device__ __forceinline__ void walk_block(const FrameParams &fp, const MapDev &md, int blk, int rblk, WalkShared &ws)
 {
     unsigned long long *t_key = ws.t_key;
@@ -3536,7 +3534,7 @@ hipError_t launch_loss(const FrameParams &fp, const MapDev &md, const LossParams
 // took 62 us for 65,536 rays and 20 classes; this takes 25 us.)
 // NVL: vectors of a row per lane; row vector v belongs to lane v mod 4.
 constexpr int kBackRays = 64;               // rays per workgroup
-constexpr int kBackCells = 3 * 12 + 4 + 1;  // cells of a ray (sdf_trunc <= 6 voxel_size), odd row stride
+constexpr int kBackCells = kMaxCells | 1;    // cells of a ray, odd row stride
 
 template <int NVL>
 __global__ __launch_bounds__(4 * kBackRays) void k_backward_rays(FrameParams fp, MapDev md, LossParams lp,
@@ -3577,7 +3575,7 @@ __global__ __launch_bounds__(4 * kBackRays) void k_backward_rays(FrameParams fp,
                 if (sdf < fp.tau) inner |= 1ull << ncell;
                 ncell++;
             });
-            // (a ray within the limits has at most kMaxRuns leaf runs and fewer cells)
+            // (a ray within the limits has at most kMaxRuns leaf runs and kMaxCells cells)
             valid = started && inrange && nrun <= kMaxRuns && ncell <= kBackCells;
         }
     }
