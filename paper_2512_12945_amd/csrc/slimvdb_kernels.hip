@@ -4199,8 +4199,8 @@ __global__ __launch_bounds__(256) void k_predict(const MapDev md, const PredictP
 // wave a point 3.7e-7 and 2.7e-6.
 // Bound by the records' bytes (mean and beta once) and the outputs, and by the waves
 // in flight: five workgroups a CU need 96 registers, which the scheduling barrier
-// between the tiles keeps to (without it four, and 130 us).  50,000 points x 56
-// prototypes x 512 components take 115 us; one wave a point, which forms every dot
+// after every second tile keeps to (without it four, and 130 us; six spill 15, 122 us).
+// 50,000 points x 56 prototypes x 512 components take 114 us; one wave a point, which forms every dot
 // product and every prototype norm by itself, 960 us.  With 32 points a workgroup,
 // half the prototype traffic but a third fewer waves, 180 us.
 // Where none of the 16 points has a record nothing is contracted (2,000 such points,
@@ -4237,6 +4237,9 @@ __global__ __launch_bounds__(256, PMAX == 1024 ? 1 : 5) void k_predict_open(cons
                 q2[u] = 0.0f;
                 acc[u] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
             }
+            uint32_t row[CT];  // (32-bit offsets into the prototypes: at most 2^20 floats)
+#pragma unroll
+            for (int u = 0; u < CT; ++u) row[u] = p0 + 16 * u + c < P ? (uint32_t)(p0 + 16 * u + c) * (uint32_t)L : 0u;
             for (int s = w; 16 * s < L; s += 4 * U) {
                 float a[U][4], b[U][CT][4];
 #pragma unroll
@@ -4254,7 +4257,7 @@ __global__ __launch_bounds__(256, PMAX == 1024 ? 1 : 5) void k_predict_open(cons
 #pragma unroll
                     for (int u = 0; u < CT; ++u) {
                         const int p = p0 + 16 * u + c;
-                        const float *B = pp.protos + (size_t)(p < P ? p : 0) * L + k;
+                        const float *B = pp.protos + (row[u] + (uint32_t)k);
                         if constexpr (FAST) {
                             const float4 x = p < P && k < L ? *(const float4 *)B : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                             b[v][u][0] = x.x; b[v][u][1] = x.y; b[v][u][2] = x.z; b[v][u][3] = x.w;
@@ -4276,7 +4279,7 @@ __global__ __launch_bounds__(256, PMAX == 1024 ? 1 : 5) void k_predict_open(cons
                         z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v][1], y[1], z0, 0, 0, 0);
                         z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v][3], y[3], z1, 0, 0, 0);
                         acc[u] += z0 + z1;
-                        __builtin_amdgcn_sched_barrier(0);
+                        if (CT == 1 || (u & 1)) __builtin_amdgcn_sched_barrier(0);
                         q2[u] += fmaf(y[3], y[3], fmaf(y[2], y[2], fmaf(y[1], y[1], y[0] * y[0])));
                     }
                 }
