@@ -534,7 +534,7 @@ def main():
                                "20 classes as int32 labels, 10% flicker; map grows over the sweeps",
                    "points_per_step": n_pts, "voxel_size": 0.1, "sdf_trunc": 0.3, "num_classes": 20,
                    "first_timed_sweep": W,
-                   "api": "slim_integrate_sequence, all timed sweeps in one call (multi-frame passes, default 4)"},
+                   "api": "slim_integrate_sequence, all timed sweeps in one call (multi-frame passes, default 8)"},
         "voxel_updates_per_s": acc["pairs"] / el,
         "valid_points_per_s": acc["valid"] / el,
         "alg_bytes_per_step": b_alg / K,

@@ -306,7 +306,7 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
  * labels, at most 32 classes, Bayesian mode) take consecutive frames in
  * multi-frame passes (up to slim_launch_shape.pass_frames, at most 8,
  * default 8; the last frame alone): one ray walk over all their rays, one
- * plan, bucketing, leaf kernel and commit, each voxel applying its frames'
+ * plan, emission of the pairs, leaf kernel and commit, each voxel applying its frames'
  * observations frame by frame, Eq. (1)-(2) and Eq. (6) as for a frame alone.  This form returns after
  * the GPU has finished the call's work: a pass that exceeds the map's
  * capacity or staging table is not applied, and its frames and the later ones
@@ -320,21 +320,23 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
  * single-frame calls, not the overlapped form. */
 slim_status slim_integrate_sequence(slim_map *map, const slim_frame *frames_host, int32_t count, void *stream);
 
-/* Grid sizes of the grid-stride kernels of integration: leaf planning and pair
- * bucketing blocks, and leaf-kernel blocks per compute unit (1 .. 32; default 16); and
- * pass_frames, the most frames slim_integrate_sequence takes in one pass
- * (0: the default 8, 1: one at a time, at most 8).
+/* Grid sizes of the grid-stride kernels of integration: leaf planning blocks, the
+ * most blocks that write pairs into their leaves' buckets (bucket_blocks; no more
+ * are launched than there are blocks of 256 rays, and passes of
+ * slim_integrate_sequence take as many), and leaf-kernel blocks per compute unit
+ * (1 .. 32; default 16); and pass_frames, the most frames
+ * slim_integrate_sequence takes in one pass (0: the default 8, 1: one at a time, at most 8).
  * batch_mode picks the form of slim_integrate_batched: 1 one persistent launch
- * whose workgroups take ray-chunk, planning, bucketing, leaf-tile, combine and
+ * whose workgroups take ray-chunk, planning, emitting, leaf-tile, combine and
  * commit items of every map from a queue, 2 one launch per stage, 0 the
  * default (1).  In the persistent launch the three grid sizes are the numbers
- * of planning, bucketing and leaf-tile (and combine) items of the whole batch,
+ * of planning, emitting and leaf-tile (and combine) items of the whole batch,
  * shared between the maps in proportion to their rays, and walk_chunk is the
  * size of a ray-chunk item in blocks of 256 rays (1 .. 64, 0: the default 4).
  * Leaf tiles: a touched leaf with at most wave_pairs pairs is one wave's work
  * (16 .. 256, capped at 128 for accumulated frames; 0: the cap), and a sorted
- * leaf with more than slab_pairs pairs is split into one item per x-slab
- * (512 .. 2048; 0: 2048, what the leaf kernel's LDS holds).
+ * leaf with more than slab_pairs pairs is split into one item per x-slab, or in a
+ * frame of more than 65,536 points on its own per range of its pairs (512 .. 2048; 0: 2048, what the leaf kernel's LDS holds).
  * Results do not depend on any of them (each voxel's sums are exact integers
  * or formed in frame and point order); they only move time.  NULL restores
  * the defaults.  Batched calls use the shape of maps[0]. */
@@ -347,8 +349,9 @@ slim_status slim_set_launch_shape(slim_map *map, const slim_launch_shape *shape)
 /* Kernel timing (measurement support, not part of the method).  While
  * enabled, slim_integrate (and each pass or single frame of
  * slim_integrate_sequence) brackets each stage of integration with HIP events
- * on the stream it launches on: index 0 ray walk and pair emission, 1 leaf
- * planning, 2 pair bucketing, 3 leaf kernel (accumulation, or sort and
+ * on the stream it launches on: index 0 ray walk, 1 leaf planning, 2 pairs
+ * written to their leaves' buckets (with the softmax of logit rows, and the
+ * binning of large leaves), 3 leaf kernel (accumulation, or sort and
  * combine), 4 wave-per-voxel combine (no kernel, and about zero time, for
  * frames whose leaf kernel combines its voxels itself), 5 commit.
  * slim_profile_read returns the accumulated per-stage time in milliseconds

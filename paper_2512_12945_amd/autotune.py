@@ -6,7 +6,7 @@ A shape (``slim_set_launch_shape``) has three kinds of knobs:
   work items of every map from a queue (batch_mode 1), or one launch per stage
   for all maps (batch_mode 2);
 * the work split: the ray-chunk size of the walk items (walk_chunk, in blocks
-  of 256 rays) and the numbers of planning, bucketing and leaf-tile items
+  of 256 rays) and the numbers of planning, emitting and leaf-tile items
   (grid sizes of the per-stage form);
 * the leaf tiles: the most pairs of a leaf done by one wave (wave_pairs) and
   the pairs above which a sorted leaf is split into x-slab items (slab_pairs).

@@ -33,14 +33,14 @@ static_assert(kMaxCells <= kVisitShift, "a ray's cells fit the record's bits");
 constexpr int kLeafThreads = 256;
 constexpr int kLeafBatch = 8;                // loads in flight per thread in the leaf kernel
 constexpr int kLeafLdsPairs = kLeafBatch * kLeafThreads;  // pairs a leaf holds in LDS at once
-// Binned frames: bucketed (then binned) pairs per work item of a large leaf.
+// Binned frames: pairs of a large leaf per work item.
 // Whole bins are dealt, so an item may hold up to a bin more; a quarter of LDS
 // is left for that.
 constexpr int kRangePairs = kLeafLdsPairs - kLeafLdsPairs / 4;
 // bits of the render's filters: leaves (32 KB), then blocks of leaves (4 KB)
 constexpr int kFilterLog2 = 18, kFilterBlockLog2 = 15;
 constexpr int kFilterWords = ((1 << kFilterLog2) + (1 << kFilterBlockLog2)) / 32;
-constexpr int kNumProfiled = 6;  // timed stages: walk, plan, bucketing, leaf kernel, voxel combine, commit
+constexpr int kNumProfiled = 6;  // timed stages: walk, plan, emit, leaf kernel, voxel combine, commit
 constexpr int kAccFrames = 8;        // frames of a pass the accumulating leaf kernel takes
 constexpr int kAccWavePairs = 128;   // accumulated leaves with at most this many pairs are one wave's work
 constexpr int kPassFrames = 8;               // most frames integrated in one pass
@@ -220,7 +220,7 @@ struct MapDev {
     uint32_t *pair_key;   // leaf-kernel scratch: sorted keys of bins beyond LDS, wave-combine input
     float *pair_tsdf;     // and their truncated distances
     uint2 *srt_kv;        // pairs grouped by leaf: (key, truncated distance bits)
-    int32_t *srt_lab;     // accumulated frames: int32 label of each bucketed pair; binned frames: 512 bin
+    int32_t *srt_lab;     // accumulated frames: int32 label of each pair; binned frames: 512 bin
                           // starts at the bucket of each large leaf
     uint32_t *tmp_key;    // scratch of large leaves: pairs binned by voxel offset
     float *tmp_tsdf;
@@ -259,7 +259,7 @@ struct MapBatch {
 // batched launch (results do not depend on any of them).
 struct LaunchShape {
     int plan_blocks;    // leaf planning
-    int bucket_blocks;  // pair bucketing
+    int bucket_blocks;  // pairs into their buckets (a frame of a pass: as many as its blocks of rays)
     int leaf_blocks;    // per-leaf sort and combine
     int persistent;     // batched calls: 1 one persistent launch, 0 one launch per stage
     int walk_chunk;     // persistent: walk blocks (256 rays each) per ray-chunk item
@@ -273,7 +273,7 @@ struct LaunchShape {
 struct BatchPlan {
     int nmaps;
     int walk_blocks;                 // total blocks of the walk kernel
-    int plan_blocks, bucket_blocks;  // grids of planning and bucketing
+    int plan_blocks, bucket_blocks;  // grids of planning and emitting
     int ngroups;
     int group_kind[17];                   // leaf-kernel variant of each group
     int group_begin[17], group_size[17];  // slice of the device subset array
@@ -295,7 +295,7 @@ hipError_t launch_integrate_batched(const MapBatch &mb, const BatchPlan &plan, c
 //   w = the counter to wait for | its target << 16, or kPersistNoDep;
 // and a control block of uint32 words, zero at launch:
 //   [0] next item, [1] abort flag, [2 + map * kPersistStages + stage] finished items.
-constexpr int kPersistStages = 6;  // walk, planning, bucketing, leaf kernel, voxel combine, commit
+constexpr int kPersistStages = 6;  // walk, planning, emitting, leaf kernel, voxel combine, commit
 constexpr uint32_t kPersistEnd = 0xFFFFFFFFu;
 constexpr uint32_t kPersistNoDep = 0xFFFFFFFFu;
 constexpr int kPersistCtlAbort = 1;

@@ -1123,7 +1123,7 @@ slim_status slim_integrate_batched(slim_map *const *maps, int32_t nmaps, const s
     }
     const LaunchShape shape = m0->shape;
     // persistent launch: the work items of every map, stage after stage; the
-    // planning, bucketing and leaf-tile items of the batch are shared between
+    // planning, emitting and leaf-tile items of the batch are shared between
     // the maps in proportion to their walk blocks (so the item list, like the
     // graph, depends only on the walk grid, the variants and the shape)
     std::vector<uint4> items;

@@ -311,7 +311,7 @@ __device__ void block_scan512(const uint32_t *in, uint32_t *out, uint32_t *wsum)
 }
 
 // ---------------------------------------------------------------------------
-// 1. ray walk and pair emission
+// 1. ray walk
 // ---------------------------------------------------------------------------
 
 constexpr int kWaveItemPairs = 256;  // leaves with at most this many pairs are one wave's work
@@ -770,8 +770,8 @@ __global__ __launch_bounds__(256) void k_leaf_plan_batch(MapBatch mb)
 // point hold 32 classes).  Formed here once per point, an observation costs the
 // combine one row of additions; formed there, once per observation (9 per point),
 // its exponentials and divisions bound the leaf kernel.  65,536 rays, 20 classes:
-// leaf kernel 96 -> 43 us (vector rows included), bucketing 7 -> 11 us; 131,071 rays:
-// 200 -> 65 us, 9 -> 16 us.
+// leaf kernel 96 -> 43 us (vector rows included) for 4 us more in this stage; 131,071
+// rays: 200 -> 65 us for 7.
 __host__ __device__ inline int soft_stride(int K) { return (K + 3) & ~3; }
 
 __host__ __device__ inline bool soft_rows(const FrameParams &fp)
@@ -812,7 +812,7 @@ __device__ __forceinline__ void softmax_rows_range(const FrameParams &fp, const 
 // runs and bucket starts are read before the walk, side by side.  Written straight
 // to the buckets, the pairs pass through memory once; as 16-byte records in walk
 // order, bucketed by a launch of their own, an 8-sweep pass took 94 us for the walk
-// and 56 for the bucketing, now 70 and 51; 16 maps 103 and 33, now 52 and 52.
+// and 56 for the bucketing, now 70 and 52; 16 maps 103 and 33, now 52 and 38.
 __device__ __forceinline__ void ray_emit_block(const FrameParams &fp, const MapDev &md, int blk, int rblk)
 {
     const int i = blk * blockDim.x + threadIdx.x;
@@ -923,7 +923,7 @@ __global__ __launch_bounds__(kWalkThreads) void k_ray_emit_batch(MapBatch mb)
 // every pair of the leaf to find its own, twice when they are many: at 640x480
 // pixels and 2 cm voxels the 206 leaves touched hold up to 61,000 pairs, and
 // those reads were most of the leaf kernel's time.  These two kernels group the
-// pairs by voxel offset first, a workgroup per range of kRangePairs bucketed
+// pairs by voxel offset first, a workgroup per range of kRangePairs of a bucket's
 // pairs: k_leaf_count counts each range's offsets, k_leaf_bin forms the leaf's
 // bin starts from its ranges' counts (no atomics between workgroups) and moves
 // the range's pairs to their bins.  The leaf kernel's items are then ranges of
@@ -2845,7 +2845,7 @@ __global__ __launch_bounds__(64) void k_frame_commit_batch(MapBatch mb)
 //
 // One launch integrates one frame into each of many maps.  Its workgroups stay
 // resident and take work items from an integer queue in order: the ray-chunk
-// items of every map's walk, then every map's planning, bucketing, leaf-tile,
+// items of every map's walk, then every map's planning, emitting, leaf-tile,
 // voxel-combine and commit items.  An item of a stage starts once all items of
 // the previous stage of the same map have finished (a per-map, per-stage
 // counter), so the stages of different maps overlap and a large frame does
@@ -3222,9 +3222,15 @@ static void launch_leaf_batch(int kind, const MapBatch &mb, int blocks, hipStrea
 
 // Frames whose large leaves are binned.  The two launches cost about 10 us and
 // save what the x-slab items read more than once, which grows with the square of
-// the points per leaf: at 33,127 pixels (L = 100) the leaf stage takes 29 us with
-// slabs and 27 us binned, at 65,536 LiDAR rays with class rows 103 and 111 us, at
-// 131,071 rays 262 and 222 us, at 307,200 pixels (L = 512) 544 and 104 us.
+// the points per leaf.  The points of the frame stand for those of a leaf, which the
+// host does not know.  A frame with slabs and binned: LiDAR rays with 20-class rows,
+// voxel 0.1 m, 66,000 rays 73 and 79 us, 80,000 81 and 85, 100,000 94 and 92, 131,071
+// 120 and 110; voxel 0.2 m, 66,000 rays 186 and 121, 131,071 498 and 197; depth images
+// at 2 cm, 100-d embeddings, 19,200 pixels 75 and 86, 33,338 101 and 93, 62,208 141 and
+// 110, 76,800 165 and 123, 512-d, 307,200 pixels 544 and 104 in the leaf stage alone.
+// The line keeps sweeps of up to 65,536 rays with the slabs; dense images would gain
+// from half of it on.  Batched and persistent calls always have the slabs: they have no
+// stages for the binning.
 constexpr int kBinPoints = 65536;
 
 static bool bins_large_leaves(const FrameParams &fp) { return !accum_path(fp) && fp.n > kBinPoints; }
@@ -4478,7 +4484,7 @@ __device__ __forceinline__ void render_step(float &tx, float &ty, float &tz, uin
 // is the choice of the axis, three conditional additions, one to the fields and one
 // test of their upper bits; lookups and the test for the ray's end wait for the way
 // out.  In a leaf of the map 8 cells are stepped through before their occupancy, then
-// their D, are read side by side.  1209 x 448 pixels over 8,200 leaves 675 -> 403 us with
+// their D, are read side by side.  1209 x 448 pixels over 8,200 leaves 675 -> 402 us with
 // the filters' launch (with the filters cleared and built by two launches 420, then 474
 // with one cell's reads at a time, 468 with 4 cells and 8 waves per SIMD).  (Jumping to the way out of
 // an empty block in closed form, exact while tm stays in a binade, took 1,143 us: too
